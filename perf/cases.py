@@ -1,0 +1,214 @@
+"""Performance cases of kvx: one store or load call each, as a serving replica makes it.
+
+A case names the operation, the pool it runs against, the layout and the size:
+
+* ``op``: "store" / "load" (paged KV blocks to and from packed chunks), "load_noalloc" (the restore that
+  allocates nothing), "store_state" / "load_state" (recurrent-state snapshots);
+* ``pool``: "staged" (pinned host pool, DMA copies: the default), "zero_copy" (pinned host pool, kernels over the
+  link) or "device" (a chunk tier in HBM);
+* KV cases: ``L H D E BS C`` as in ``make_layout``, ``nhd`` (token-major blocks), ``tokens`` (prefix length, any
+  number: the last chunk and block may be partial) and ``shuffled`` (pool slots in random order, as an LRU pool
+  hands them out; otherwise consecutive, as in an empty pool);
+* state cases: ``G`` recurrent layers, ``page`` bytes per layer and snapshot, ``snapshots`` in one request.
+
+A pass over a host pool ends with the caller's stream synchronised: whoever consumes the pool's bytes, or answers
+a replica's request, completes the call on the host first.  A pass over a device pool only enqueues.
+
+Values are opaque bytes to this path (moved, never computed), so the inputs are random bits and every output is
+compared exactly.
+"""
+import ctypes
+import math
+
+import numpy as np
+import torch
+
+from paper_2609_15021_amd import kvx
+
+DEVICE = "cuda:0"
+
+# Layouts.  B27: the 27B-class GQA layout (bf16, 256 KiB per token); its shards hold H/2 ... H/8 heads of a
+# tensor-parallel replica.  PAPER: the FP8 attention layers of the shared-cache deployment, 32-token pages and
+# 1,568-token chunks.  TINY: the smallest layout that the tests use.
+B27 = dict(L=64, H=8, D=128, E=2, BS=16, C=256, nhd=False)
+PAPER = dict(L=16, H=4, D=256, E=1, BS=32, C=1568, nhd=True)
+TINY = dict(L=2, H=2, D=64, E=2, BS=16, C=256, nhd=False)
+
+
+def _kv(name, op, pool, layout, tokens, shuffled, **changes):
+    return dict(layout, **changes, name=name, op=op, pool=pool, tokens=tokens, shuffled=shuffled)
+
+
+def listed():
+    return [
+        # The smallest requests: a 4,096-token prefix of the tiny layout (4 MiB).  Latency counts here.
+        _kv("store_staged_tiny", "store", "staged", TINY, 4096, True),
+        # One session turn's new tokens on one rank of a 4-way sharded replica, into the slots that LRU freed.
+        _kv("load_staged_shard4_turn", "load", "staged", B27, 2048 + 37, True, H=2),
+        # A replica publishes a prefix at the 27B-class layout, and another restores a longer one.
+        _kv("store_staged_27b_8k", "store", "staged", B27, 8192, False),
+        _kv("load_staged_27b_32k", "load", "staged", B27, 32768, False),
+        # Aligned recovery of a hybrid model: the one snapshot at the restored boundary.
+        dict(name="load_state_staged_1", op="load_state", pool="staged", G=48, page=3207168, snapshots=1),
+        # Zero-copy: one rank of an 8-way sharded replica (one KV head: 4 KiB slabs), and the deployment's own
+        # token-major FP8 layout with a partial last chunk.
+        _kv("store_zero_copy_shard8", "store", "zero_copy", B27, 4096, False, H=1),
+        _kv("load_zero_copy_paper", "load", "zero_copy", PAPER, 5000, True),
+        # The device-resident tier: whole replica, one rank of an 8-way shard, the FP8 layout, and a small call.
+        _kv("store_device_27b_32k", "store", "device", B27, 32768, False),
+        _kv("load_device_shard8_128k", "load", "device", B27, 131072, True, H=1),
+        _kv("load_device_paper_128k", "load", "device", PAPER, 131072, True),
+        _kv("store_device_tiny", "store", "device", TINY, 1000, True),
+        # A restore inside code that may not allocate.
+        _kv("load_noalloc_27b_4k", "load_noalloc", "staged", B27, 4096, True),
+    ]
+
+
+def _log_uniform(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+# A drawn request moves at most this much (the largest listed ones: 8 GiB from a host pool and in HBM).
+_MOST = {"staged": 2 << 30, "zero_copy": 1 << 30, "device": 4 << 30}
+
+
+def draw(rng):
+    op = rng.choice(["store", "load", "store", "load", "store", "load", "load_noalloc", "store_state", "load_state"])
+    pool = "staged" if op == "load_noalloc" else rng.choice(["staged", "zero_copy", "device"])
+    if op.endswith("_state"):
+        while True:
+            c = dict(op=op, pool=pool, G=rng.choice([1, 8, 24, 36, 48, 64]),
+                     page=16 * _log_uniform(rng, 512, 262144), snapshots=_log_uniform(rng, 1, 16))
+            if c["G"] * c["page"] * c["snapshots"] <= _MOST[pool] // 2:
+                return c
+    while True:
+        c = dict(op=op, pool=pool, L=rng.choice([2, 16, 24, 36, 48, 64]), H=rng.choice([1, 2, 3, 4, 5, 8]),
+                 D=rng.choice([64, 80, 96, 128, 192, 256]), E=rng.choice([1, 2, 2, 4]), BS=rng.choice([8, 16, 32]),
+                 C=rng.choice([256, 256, 512, 1568]), nhd=rng.random() < 0.4,
+                 tokens=_log_uniform(rng, 64, 131072), shuffled=rng.random() < 0.6)
+        # One chunk at most 64 MiB: the largest listed one, and what the no-allocation restore takes.
+        if c["C"] * _token_bytes(c) <= 64 << 20 and c["tokens"] * _token_bytes(c) <= _MOST[pool]:
+            return c
+
+
+def _token_bytes(c):
+    return 2 * c["L"] * c["H"] * c["D"] * c["E"]
+
+
+class _DeviceMemory:
+    """The device pool's bytes for torch (keeps the pool alive)."""
+
+    def __init__(self, pool, address, nbytes):
+        self.pool = pool
+        self.__cuda_array_interface__ = dict(shape=(nbytes // 8,), typestr="<i8", data=(address, False), version=2)
+
+
+def _pool_words(pool, address, nbytes, on_device):
+    """A pool region as an int64 tensor that shares its memory and keeps the pool alive."""
+    if on_device:
+        return torch.as_tensor(_DeviceMemory(pool, address, nbytes), device=DEVICE)
+    buf = (ctypes.c_int64 * (nbytes // 8)).from_address(address)
+    buf.pool = pool
+    return torch.from_numpy(np.frombuffer(buf, dtype=np.int64))
+
+
+def _random_words(n, gen):
+    return torch.randint(-(1 << 63), (1 << 63) - 1, (n,), dtype=torch.int64, device=DEVICE, generator=gen)
+
+
+def _fill(words, gen):
+    """Random bits into a pool region (in pieces of at most 1 GiB)."""
+    for lo in range(0, words.numel(), 1 << 27):
+        part = words[lo:lo + (1 << 27)]
+        part.copy_(_random_words(part.numel(), gen))
+
+
+def _make_pool(case, layout, num_slots, **state_area):
+    if case["pool"] == "device":
+        return kvx.kv_pool_create(layout, num_slots, "zero_copy", host_kind=kvx.KV_POOL_DEVICE, **state_area)
+    return kvx.kv_pool_create(layout, num_slots, case["pool"], **state_area)
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device=DEVICE).manual_seed(seed)
+    rng = np.random.default_rng(seed)
+    on_device = case["pool"] == "device"
+    if case["op"].endswith("_state"):
+        return _prepare_state(case, gen, rng, on_device)
+    layout = kvx.make_layout(*(case[k] for k in ("L", "H", "D", "E", "BS", "C")))
+    nblk, nc = -(-case["tokens"] // case["BS"]), -(-case["tokens"] // case["C"])
+    # The replica's cache: a quarter more blocks than the prefix needs, the prefix on a random subset of them.
+    num_blocks = nblk + nblk // 4 + 1
+    table = torch.from_numpy(rng.permutation(num_blocks)[:nblk].astype(np.int32)).to(DEVICE)
+    num_slots = nc + (2 if case["shuffled"] else 0)
+    ids = rng.permutation(num_slots)[:nc] if case["shuffled"] else np.arange(nc)
+    pool = _make_pool(case, layout, num_slots)
+    info = kvx.kv_pool_get_info(pool)
+    words = _pool_words(pool, info["device_base"] if on_device else info["host_base"], info["pool_bytes"], on_device)
+    cache_words = num_blocks * case["BS"] * _token_bytes(case) // 8
+    if case["op"] == "store":
+        cache = _random_words(cache_words, gen)
+        # What a store leaves alone: the spare slots and the tail of a partial last chunk's slot.
+        slots = words.view(num_slots, -1)
+        for s in {int(ids[-1])} | set(range(num_slots)) - set(int(i) for i in ids):
+            slots[s].zero_()
+    else:
+        cache = torch.zeros(cache_words, dtype=torch.int64, device=DEVICE)
+        _fill(words, gen)
+    cache = cache.view(case["L"], -1)
+    order = kvx.KV_BLOCK_NHD if case["nhd"] else kvx.KV_BLOCK_HND
+    return dict(op=case["op"], on_device=on_device, pool=pool, ids=np.ascontiguousarray(ids, dtype=np.int64), table=table,
+                tokens=case["tokens"], cache=kvx.Cache(cache, layout, num_blocks, block_order=order),
+                out=words if case["op"] == "store" else cache)
+
+
+def _prepare_state(case, gen, rng, on_device):
+    G, page, n = case["G"], case["page"], case["snapshots"]
+    num_pages, num_slots = n + 3, n + 1
+    pages, slots = rng.permutation(num_pages)[:n].astype(np.int64), rng.permutation(num_slots)[:n].astype(np.int64)
+    # The snapshots live beside the chunks of the hybrid deployment's attention layers.
+    layout = kvx.make_layout(*(PAPER[k] for k in ("L", "H", "D", "E", "BS", "C")))
+    pool = _make_pool(case, layout, 1, num_state_slots=num_slots, state_slot_bytes=G * page)
+    info = kvx.kv_pool_get_info(pool)
+    # The state area follows the chunk slots at the next 4 KiB boundary.
+    base = info["device_base"] + -(-info["pool_bytes"] // 4096) * 4096 if on_device else info["state_host_base"]
+    words = _pool_words(pool, base, num_slots * G * page, on_device)
+    if case["op"] == "store_state":
+        buffers = _random_words(G * num_pages * page // 8, gen)
+        words.zero_()
+    else:
+        buffers = torch.zeros(G * num_pages * page // 8, dtype=torch.int64, device=DEVICE)
+        _fill(words, gen)
+    buffers = buffers.view(G, -1)
+    return dict(op=case["op"], on_device=on_device, pool=pool, pages=pages, slots=slots,
+                state=kvx.State(buffers, page, num_pages), out=words if case["op"] == "store_state" else buffers)
+
+
+def run(state):
+    op, pool = state["op"], state["pool"]
+    if op == "store":
+        kvx.kv_store(state["cache"], state["table"], state["tokens"], pool, state["ids"])
+    elif op == "load":
+        kvx.kv_load(state["cache"], state["table"], state["tokens"], pool, state["ids"])
+    elif op == "load_noalloc":
+        kvx.kv_load_noalloc(state["cache"], state["table"], state["tokens"], pool, state["ids"])
+    elif op == "store_state":
+        kvx.kv_store_state(state["state"], state["pages"], pool, state["slots"])
+    else:
+        kvx.kv_load_state(state["state"], state["pages"], pool, state["slots"])
+    if not state["on_device"]:
+        torch.cuda.current_stream().synchronize()  # completion on the host, before anyone uses the result
+    return state["out"]
+
+
+def work(case):
+    """Each payload byte is read once and written once (one of the two over the host link for a host pool)."""
+    if case["op"].endswith("_state"):
+        payload, index = case["G"] * case["page"] * case["snapshots"], 0
+    else:
+        payload, index = case["tokens"] * _token_bytes(case), 4 * -(-case["tokens"] // case["BS"])
+    return {"bytes": 2 * payload + index, "flops": 0}
+
+
+def tolerance(case):
+    return "exact"
