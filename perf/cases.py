@@ -43,6 +43,8 @@ def listed():
     return [
         # The smallest requests: a 4,096-token prefix of the tiny layout (4 MiB).  Latency counts here.
         _kv("store_staged_tiny", "store", "staged", TINY, 4096, True),
+        # A restore inside code that may not allocate.
+        _kv("load_noalloc_27b_4k", "load_noalloc", "staged", B27, 4096, True),
         # One session turn's new tokens on one rank of a 4-way sharded replica, into the slots that LRU freed.
         _kv("load_staged_shard4_turn", "load", "staged", B27, 2048 + 37, True, H=2),
         # A replica publishes a prefix at the 27B-class layout, and another restores a longer one.
@@ -55,12 +57,12 @@ def listed():
         _kv("store_zero_copy_shard8", "store", "zero_copy", B27, 4096, False, H=1),
         _kv("load_zero_copy_paper", "load", "zero_copy", PAPER, 5000, True),
         # The device-resident tier: whole replica, one rank of an 8-way shard, the FP8 layout, and a small call.
+        # Large device cases come last: the driver clears freed device memory with DMA for seconds, which slows the
+        # DMA copies of a case that follows.
         _kv("store_device_27b_32k", "store", "device", B27, 32768, False),
         _kv("load_device_shard8_128k", "load", "device", B27, 131072, True, H=1),
         _kv("load_device_paper_128k", "load", "device", PAPER, 131072, True),
         _kv("store_device_tiny", "store", "device", TINY, 1000, True),
-        # A restore inside code that may not allocate.
-        _kv("load_noalloc_27b_4k", "load_noalloc", "staged", B27, 4096, True),
     ]
 
 
