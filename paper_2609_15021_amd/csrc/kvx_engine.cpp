@@ -26,50 +26,6 @@
 using kvx::Direction;
 using kvx::Geometry;
 
-namespace kvx {
-
-hipError_t launch_gathers(const kv_cache *cache, const int32_t *block_table, int64_t n_tokens, Direction dir,
-                          int64_t chunk0, int nchunks, const int32_t *slots, uint8_t *chunk_base, int64_t slot_stride,
-                          bool host_side, int32_t *err, hipStream_t stream) {
-    const Geometry g = geometry(cache->layout, cache->block_stride_bytes);
-    for (int layer0 = 0; layer0 < g.L; layer0 += kMaxLaunchLayers) {
-        const int nl = static_cast<int>(std::min<int64_t>(kMaxLaunchLayers, g.L - layer0));
-        const int per_launch = max_chunks_per_launch(g, nl);
-        for (int c0 = 0; c0 < nchunks; c0 += per_launch) {
-            const int nc = std::min(per_launch, nchunks - c0);
-            GatherArgs a;
-            std::memset(&a, 0, sizeof(a));
-            for (int l = 0; l < nl; ++l)
-                a.layer[l] = static_cast<uint8_t *>(cache->layer_ptrs[layer0 + l]);
-            a.chunk_base = chunk_base;
-            a.block_table = block_table;
-            a.err = err;
-            a.slot_stride = slot_stride;
-            a.block_stride = g.block_stride;
-            a.n_tokens = n_tokens;
-            a.chunk0 = chunk0 + c0;
-            a.num_blocks = cache->num_blocks;
-            a.layer0 = layer0;
-            a.nlayers = nl;
-            a.H = static_cast<int32_t>(g.H);
-            a.BS = static_cast<int32_t>(g.BS);
-            a.C = static_cast<int32_t>(g.C);
-            a.vec_per_row = static_cast<int32_t>(g.vec_per_row);
-            a.blocks_per_chunk = static_cast<int32_t>(g.blocks_per_chunk);
-            a.nchunks = nc;
-            a.nhd = cache->block_order == KV_BLOCK_NHD ? 1 : 0;
-            for (int c = 0; c < nc; ++c)
-                a.slot[c] = slots[c0 + c];
-            const hipError_t e = launch_gather(a, dir, host_side, stream);
-            if (e != hipSuccess)
-                return e;
-        }
-    }
-    return hipSuccess;
-}
-
-}  // namespace kvx
-
 namespace {
 
 constexpr int kDefaultStagingSlots = 3;
@@ -529,7 +485,7 @@ kv_status kv_pool_create(const kv_layout *layout, int64_t num_slots, const kv_po
         const bool staged = opts->mode == KV_MODE_STAGED;
         const int cpb = (staged && opts->chunks_per_batch) ? opts->chunks_per_batch : kDefaultChunksPerBatch;
         // Zero-copy launches into host memory default to the largest launch (they stride a capped grid);
-        // device-pool launches default to the staged launch shape (one workgroup per slab).
+        // device-pool launches default to the staged launch shape (one workgroup per tile).
         const int zc_chunks = (!staged && opts->chunks_per_batch) ? opts->chunks_per_batch
                               : on_device                        ? kDefaultChunksPerBatch
                                                                  : kvx::kMaxLaunchChunks;

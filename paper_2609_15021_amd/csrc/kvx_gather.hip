@@ -1,30 +1,36 @@
 // Pack (store) and unpack (load) kernels for gfx950.
 //
-// A workgroup moves one slab at a time: the (layer l, K/V, block j) piece of chunk i, i.e. the
-// bs <= BS tokens of one paged block for one layer and one of K/V.  On the cache side the
-// slab is the contiguous [H][BS][D] region of that block (HND, the paper's replica layout,
-// Table 1); on the chunk side it is the contiguous [bs][H][D] run of token-major rows
-// inside plane (l, kv) of the chunk.  The slab is therefore contiguous on both sides and
-// differs only by a permutation of D*E-byte rows: cache row (h, s) <-> chunk row (s, h).
+// On the cache side the K (or V) slab of one paged block is the contiguous [H][BS][D] region of that
+// block (HND, the paper's replica layout, Table 1) or [BS][H][D] (NHD, token-major); on the chunk side a
+// plane (layer, K/V) of a chunk is one contiguous run [r][H][D] of token-major rows, the slabs of the
+// chunk's blocks one after the other.  A slab differs between the sides only by a permutation of
+// D*E-byte rows: cache row (h, s) <-> chunk row (s, h); for NHD blocks not at all.
 //
-// Token-major (NHD) cache blocks hold the slab's rows already in chunk order: the slab
-// is then a straight contiguous copy.  For HND blocks, lanes walk the chunk side in order
-// in both directions: the pool/staging side (host memory over PCIe in zero-copy mode) is
-// read or written in contiguous 1 KiB-per-wave runs, and the cache side in whole-row runs
-// (256 bytes at D*E = 256) spread over the slab's H head regions.  Measured on MI355X with
-// both orders running on the same cache allocations, this order is 3-4% faster for unpack
-// than walking the cache side (whose writes are then contiguous) on every allocation, and
-// 1-2% faster for pack.  Rows are >= 16 bytes and moved as 16-byte vectors, so no LDS
-// transpose is needed for coalescing (staging through LDS was measured slower).
+// A plane is cut into tiles of 256 16-byte vectors (4 KiB) in chunk order, wherever its blocks end, and
+// a workgroup moves one tile, one vector per lane: the chunk side (host memory over PCIe in zero-copy
+// mode) is read or written in contiguous 1 KiB-per-wave runs, the cache side in whole rows.  HBM bounds
+// the device-side launches.  With one short tile per workgroup the tiles in flight are neighbours and
+// every lane is busy at any slab size.  Measured on MI355X, paired on the same allocations with the
+// earlier split (one slab of a block per workgroup, moved 4 KiB at a time, 5 resident per CU), pack /
+// unpack TB/s read + written, before -> after:
+//   32 KiB slabs (27B-class layout, 2 GiB)         5.75 -> 6.13 / 5.5-5.9 -> 6.0
+//   32 KiB NHD slabs (FP8, 32-token pages, 2 GiB)  5.82 -> 6.26 / 5.32 -> 5.98
+//   8 KiB slabs (two KV heads)                     4.98 -> 6.13 / 5.05 -> 5.68
+//   4 KiB slabs (one KV head)                      3.43 -> 5.92 / 3.45 -> 5.47
+//   2 KiB slabs (one KV head, FP8)                 1.92 -> 5.34 / 1.89 -> 5.03
+//   3,840-byte slabs of 160-byte rows              3.12 -> 5.07 / 2.98 -> 4.62
+// Other tiles, paired the same way (geometric mean over twelve layouts against the earlier split, pack /
+// unpack; 4 KiB: 1.46 / 1.42): 1 KiB 1.44 / 1.37, 2 KiB 1.44 / 1.39, 8 KiB 1.45 / 1.40 with 512 lanes,
+// 1.39 / 1.37 with two vectors per lane.  Handing each XCD 2, 4, 8 or 16 consecutive tiles changed pack by
+// less than 1% and cost unpack 2-3%.
 // Values are moved as integers only: no float register ever holds them (NaN payloads, -0
 // and subnormals survive).
 //
-// Index math is one division at thread start; afterwards every step is an addition with
-// carry.  Streaming data is read and written nontemporally.  Device-side (staged) launches
-// run one workgroup per slab and cap residency at 5 workgroups per CU (KVX_LDS_RESERVE).
-// Host-side (zero-copy) launches run a few dozen workgroups that stride over the slabs
-// (KVX_HOST_WGS_*): the link bounds them, and the rest of the chip stays free.
+// Streaming data is read and written nontemporally.  Host-side (zero-copy) launches run a few
+// dozen workgroups that stride over the tiles (KVX_HOST_WGS_*): the link bounds them, and the rest of
+// the chip stays free.
 #include <algorithm>
+#include <cstring>
 
 #include "kvx_internal.h"
 
@@ -35,39 +41,43 @@ namespace {
 // One 16-byte vector as a native 128-bit register tuple (kept in VGPRs; never a float).
 typedef uint32_t vec16 __attribute__((ext_vector_type(4)));
 
-// Compile-time tuning knobs: vectors each thread loads before storing (a full tile of
-// kThreads*U vectors; 1 measured best) and streaming (nontemporal) access on the read and
-// write side.
-#ifndef KVX_UNROLL
-#define KVX_UNROLL 1
-#endif
+// Compile-time tuning knobs: streaming (nontemporal) access on the read and write side.
 #ifndef KVX_NT_LOAD
 #define KVX_NT_LOAD 1
 #endif
 #ifndef KVX_NT_STORE
 #define KVX_NT_STORE 1
 #endif
-// Dynamic LDS reserved per workgroup to cap the workgroups resident per CU (only the unpack of
-// token-major slabs uses it, as a slab buffer):
-// 32 KiB of the CU's 160 KiB allows 5 (20 waves per CU).  Measured on MI355X with the
-// 27B-class layout, variants alternating on the same cache allocations in one process: 5
-// resident workgroups moved 4.2-4.6% more than 4 on two machines and the same on two others,
-// while 6, 7 and 8 lose on unpack (-2% to -5% against 4), as does an uncapped launch: fewer
-// concurrent 32 KiB streams per CU keep the HBM read/write mix efficient, too few leave HBM idle.
-#ifndef KVX_LDS_RESERVE
-#define KVX_LDS_RESERVE 32768
+// Dynamic LDS (unused) reserved per workgroup of a device-side unpack, to cap the workgroups resident per
+// CU: 26 KiB of the CU's 160 KiB allows 6 (24 waves).  Paired over twelve layouts, 6 unpacked
+// 1.4% more than 8 (the hardware's limit: 32 waves) and 0.4% more than 7, and 3-4% more on the 32 KiB slabs;
+// pack lost 7% with 6 and takes no cap.
+#ifndef KVX_LDS_RESERVE_UNPACK
+#define KVX_LDS_RESERVE_UNPACK 26624
 #endif
-// Workgroups of a host-side (zero-copy) pack / unpack launch; each strides over the
-// launch's slabs (0: one workgroup per slab).  Measured on MI355X at the 27B-class layout
-// (one workgroup per slab: store 54.5, load 55.9 GB/s): 64 for pack gives 55.9 GB/s (16:
-// 49.8, 256: 54.7); 32 for unpack gives 57.0 GB/s (16: 44, 64 to 256: 57.5) and, with
-// a staged store running at the same time, lets both directions share the link.
+#ifndef KVX_LDS_RESERVE_PACK
+#define KVX_LDS_RESERVE_PACK 0
+#endif
+// Workgroups of a host-side (zero-copy) pack / unpack launch; each strides over the launch's tiles
+// with the next tile's reads in flight.  Measured on MI355X at the 27B-class layout: 64 for pack gives
+// 57.0 GB/s (48: 56.9, 32: 52.9).  Unpack is chosen by what a staged store running at the same time
+// leaves it: 16 gives 57.1 GB/s alone and 99.8 in total (15: 56.8 and 92.7, 17: 57.2 and 91.1, 18: 57.2
+// and 78.7, 32: 57.5 and 59.6); the earlier kernel took 32 workgroups for 57.0 and 97.2.  Where each lane
+// has its own block (see start_tile) the wait for its table entry also waits for a tile's data, so it
+// takes twice as many for the same rate (160-byte rows: 16 move 47 GB/s, 32 move 56; before, 40).
 #ifndef KVX_HOST_WGS_PACK
 #define KVX_HOST_WGS_PACK 64
 #endif
 #ifndef KVX_HOST_WGS_UNPACK
-#define KVX_HOST_WGS_UNPACK 32
+#define KVX_HOST_WGS_UNPACK 16
 #endif
+#ifndef KVX_HOST_WGS_UNPACK_LANES
+#define KVX_HOST_WGS_UNPACK_LANES 32
+#endif
+#ifndef KVX_TILE_VECS
+#define KVX_TILE_VECS 256
+#endif
+constexpr int kTileVecs = KVX_TILE_VECS;  // 16-byte vectors of a tile: one per lane of a workgroup
 
 __device__ __forceinline__ vec16 load16(const vec16 *p) {
 #if KVX_NT_LOAD
@@ -93,240 +103,269 @@ __device__ __forceinline__ void store16(vec16 *p, vec16 v) {
 constexpr int kCachePolicyNtSc1 = 2 | 16;  // CDNA3/4 cache-policy bits: NT = 2, SC1 = 16
 constexpr int kRawBufferFlags = 0x00020000;  // descriptor word 3 of a raw (untyped) buffer
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_buffer(uint8_t *slab, int64_t bytes) {
+__device__ __forceinline__ void store16_nt_sc1(uint8_t *base, int64_t bytes, int vec, vec16 v) {
     // bytes < 2^31: validation caps a block at 2 GiB, so a K or V slab at 1 GiB.
-    return __builtin_amdgcn_make_buffer_rsrc(slab, 0, static_cast<int>(bytes), kRawBufferFlags);
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(base, 0, static_cast<int>(bytes), kRawBufferFlags);
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, vec * 16, 0, kCachePolicyNtSc1);
 }
 
-__device__ __forceinline__ void store16_cache(__amdgpu_buffer_rsrc_t slab, int vec, vec16 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, slab, vec * 16, 0, kCachePolicyNtSc1);
+// n / d for 0 <= n < 2^31 with the divisor's host-computed constants (Granlund and Montgomery, "Division
+// by Invariant Integers using Multiplication", PLDI 1994, Theorem 4.2 with N = 31).
+__device__ __forceinline__ int divide(int n, const Divisor &d) {
+    return static_cast<int>(__umulhi(static_cast<uint32_t>(n) << 1, d.mul) >> d.shift);
 }
 
-// Chunk-side stores of pack.  Into mapped pinned host memory (zero-copy) they take the same
-// "nt sc1" policy, which moved 57.1 GB/s over the link against 55.7-55.9 with plain nontemporal
-// stores (56.8 without either bit); into device staging plain nontemporal stores measured the same
-// as any policy.
-template <bool HOST_SIDE>
-__device__ __forceinline__ void store16_chunk(vec16 *base, __amdgpu_buffer_rsrc_t slab, int vec, vec16 v) {
-    if constexpr (HOST_SIDE)
-        __builtin_amdgcn_raw_buffer_store_b128(v, slab, vec * 16, 0, kCachePolicyNtSc1);
-    else
-        store16(base + vec, v);
-}
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Walks chunk-order vector indices v = t, t + kThreads, t + 2*kThreads, ... of one slab,
-// maintaining (s, h, col) with v = (s*H + h)*VR + col.
-struct RowWalker {
-    int s, h, col;
-    int VR, H;
-    int dcol, ds0, dh0, ds1, dh1;  // per-step increments (without / with a column carry)
+// Block ids are read-only for the launch: the constant address space makes a uniform read a scalar load.
+typedef const __attribute__((address_space(4))) int32_t *TablePtr;
 
-    __device__ RowWalker(int v, int vec_per_row, int heads) : VR(vec_per_row), H(heads) {
-        int q = v / VR;
-        col = v - q * VR;
-        s = q / H;
-        h = q - s * H;
-        int dq = kThreads / VR;
-        dcol = kThreads - dq * VR;
-        ds0 = dq / H;
-        dh0 = dq - ds0 * H;
-        ds1 = (dq + 1) / H;
-        dh1 = (dq + 1) - ds1 * H;
-    }
-
-    __device__ void advance() {
-        col += dcol;
-        int ds = ds0, dh = dh0;
-        if (col >= VR) {
-            col -= VR;
-            ds = ds1;
-            dh = dh1;
-        }
-        h += dh;
-        s += ds;
-        if (h >= H) {
-            h -= H;
-            s += 1;
-        }
-    }
-
-    // 16-byte-vector offset of the current element inside the cache-side [H][BS][D] slab.
-    __device__ int cache_vec(int BS) const { return (h * BS + s) * VR + col; }
+// A tile on its way: kTileVecs chunk-side vectors of one plane (fewer at the plane's end), one per lane.
+struct Tile {
+    uint8_t *chunk;  // the tile's first byte on the chunk side
+    uint8_t *cache;  // the layer's K (or V) slab of block 0
+    vec16 data;
+    int left;        // vectors in the tile
+    int pos;         // this lane's vector inside its block's slab
+    int32_t block;   // the block id from the table (not yet checked)
 };
 
-template <int DIR, int U, bool HOST_SIDE>
-__device__ __forceinline__ void move_slab(const GatherArgs &a, int c, int ll, int kv, int j);
-
-// HOST_SIDE marks launches whose chunk side is mapped pinned host memory (zero-copy mode);
-// the body is the same, the instantiation (and launch occupancy) is separate.
-template <int DIR, int U, bool HOST_SIDE>
-__device__ __forceinline__ void move_slab_id(const GatherArgs &a, int64_t id) {
-    // Slab id -> (chunk c, layer ll, kv, block j); j varies fastest so consecutive ids
-    // touch consecutive chunk-side regions.
-    const int bpc = a.blocks_per_chunk;
-    const int j = static_cast<int>(id % bpc);
-    int64_t rest = id / bpc;
-    const int kv = static_cast<int>(rest & 1);
-    rest >>= 1;
-    const int ll = static_cast<int>(rest % a.nlayers);
-    const int c = static_cast<int>(rest / a.nlayers);
-    move_slab<DIR, U, HOST_SIDE>(a, c, ll, kv, j);
+// 16-byte-vector offset in the cache-side slab of the slab's chunk-order vector p: chunk row (s, h) =
+// (p / VR / H, p / VR % H) is cache row (h, s); token-major slabs are in chunk order already.
+__device__ __forceinline__ int cache_vec(const GatherArgs &a, int p) {
+    if (a.nhd)
+        return p;
+    const int row = divide(p, a.by_row), s = divide(row, a.by_head);
+    return ((row - s * a.H) * a.BS + s) * a.vec_per_row + (p - row * a.vec_per_row);
 }
 
-template <int DIR, int U, bool HOST_SIDE>
-__global__ __launch_bounds__(kThreads) void gather_kernel(const GatherArgs a) {
-    if constexpr (HOST_SIDE) {
-        // A capped grid strides over the slabs: the link, not the number of waves in flight,
-        // bounds these launches, and the CUs they leave free run other streams' kernels.
-        const int64_t total = static_cast<int64_t>(a.nchunks) * a.nlayers * 2 * a.blocks_per_chunk;
-        for (int64_t id = blockIdx.x; id < total; id += gridDim.x)
-            move_slab_id<DIR, U, HOST_SIDE>(a, id);
+// Byte offset of the tile's block in the layer buffer.  bad: the id is outside the cache (flagged in the
+// pool's error word); the offset is then block 0's, so that a read through it stays in bounds.
+__device__ __forceinline__ int64_t block_offset(const GatherArgs &a, const Tile &t, bool &bad) {
+    bad = t.block < 0 || t.block >= a.num_blocks;
+    if (bad)
+        __hip_atomic_store(a.err, KV_ASYNC_BAD_BLOCK, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return bad ? 0 : t.block * a.block_stride;
+}
+
+// Start tile x of plane `plane` (2*layer + kv) of launch chunk c, x < ceil(plane vectors / kTileVecs): find
+// its block and issue its reads.  Lanes beyond the plane's end read the tile's last vector again (no
+// branch around the load).  WAVE: a slab is a whole number of waves' vectors, so that a wave's 64 vectors
+// lie in one block and its table entry and cache base are scalars; otherwise each lane has its own.
+template <int DIR, bool WAVE>
+__device__ __forceinline__ void start_tile(const GatherArgs &a, int c, int plane, int x, Tile &t) {
+    const int32_t slot = a.slot[c];
+    uint8_t *const layer = a.layer[plane >> 1];
+    // Everything a tile reads from the arguments is needed in scalar registers here, so that the scalar loads
+    // go out together: left to itself the compiler spread them over five dependent waits.
+    asm volatile("" ::"s"(slot), "s"(layer), "s"(a.chunk_base), "s"(a.block_table), "s"(a.slot_stride),
+                 "s"(a.block_stride), "s"(a.num_blocks), "s"(a.plane0), "s"(a.nchunks), "s"(a.C), "s"(a.last_r),
+                 "s"(a.blocks_per_chunk), "s"(a.token_vecs), "s"(a.slab_vecs), "s"(a.H), "s"(a.BS),
+                 "s"(a.vec_per_row), "s"(a.by_slab.mul), "s"(a.by_slab.shift), "s"(a.by_row.mul), "s"(a.by_row.shift),
+                 "s"(a.by_head.mul), "s"(a.by_head.shift), "s"(a.nhd), "s"(a.long_plane));
+    const int r = c == a.nchunks - 1 ? a.last_r : a.C;  // tokens in the chunk
+    const int64_t base = static_cast<int64_t>(x) * kTileVecs;
+    const int64_t plane_vecs = static_cast<int64_t>(r) * a.token_vecs;
+    t.left = static_cast<int>(min(plane_vecs - base, static_cast<int64_t>(kTileVecs)));
+    // The tile's first block and the first vector inside its slab.
+    int j0;
+    if (a.long_plane) {
+        // Beyond divide()'s range: a rounded quotient, one too large at most.
+        j0 = uniform(static_cast<int>(static_cast<double>(base) / a.slab_vecs));
+        if (static_cast<int64_t>(j0) * a.slab_vecs > base)
+            --j0;
     } else {
-        move_slab_id<DIR, U, HOST_SIDE>(a, blockIdx.x);  // one workgroup per slab
+        j0 = divide(static_cast<int>(base), a.by_slab);
+    }
+    const int first = static_cast<int>(base - static_cast<int64_t>(j0) * a.slab_vecs);
+    t.chunk = a.chunk_base + slot * a.slot_stride + ((a.plane0 + plane) * plane_vecs + base) * 16;
+    t.cache = layer + (plane & 1) * (static_cast<int64_t>(a.slab_vecs) * 16);
+    const TablePtr table = (TablePtr)(a.block_table + static_cast<int64_t>(c) * a.blocks_per_chunk + j0);
+
+    const int v = min(static_cast<int>(threadIdx.x), t.left - 1);
+    if (DIR == kUnpack)
+        t.data = load16(reinterpret_cast<const vec16 *>(t.chunk) + v);
+    if constexpr (WAVE) {
+        // left is a multiple of 64 unless the last block is partial, and its wave then lies in that block.
+        const int wave = first + min(uniform(static_cast<int>(threadIdx.x) & ~63), (t.left - 1) & ~63);
+        const int j = divide(wave, a.by_slab);
+        t.block = table[j];
+        t.pos = wave - j * a.slab_vecs + (v & 63);
+    } else {
+        const int j = divide(first + v, a.by_slab);
+        t.block = table[j];
+        t.pos = first + v - j * a.slab_vecs;
+    }
+    if (DIR == kPack) {
+        bool bad;
+        const int64_t off = block_offset(a, t, bad);
+        t.data = load16(reinterpret_cast<const vec16 *>(t.cache + off) + cache_vec(a, t.pos));
+        // A block id outside the cache: no cache byte is passed on and the chunk gets zeros, not the stale
+        // staging or pool bytes of another request.
+        if (bad)
+            t.data = vec16{0u, 0u, 0u, 0u};
     }
 }
 
-template <int DIR, int U, bool HOST_SIDE>
-__device__ __forceinline__ void move_slab(const GatherArgs &a, int c, int ll, int kv, int j) {
-    const int bpc = a.blocks_per_chunk;
-
-    const int64_t i = a.chunk0 + c;  // global chunk index
-    const int64_t remaining = a.n_tokens - i * a.C;
-    const int64_t r = remaining < a.C ? remaining : a.C;  // tokens in chunk i
-    const int64_t tok0 = static_cast<int64_t>(j) * a.BS;  // first token of the slab in the chunk
-    if (tok0 >= r)
+// Write a started tile to its place.
+template <int DIR, bool WAVE, bool HOST_SIDE>
+__device__ __forceinline__ void finish_tile(const GatherArgs &a, const Tile &t) {
+    const int v = static_cast<int>(threadIdx.x);
+    if (v >= t.left)
         return;
-    const int bs = static_cast<int>((r - tok0) < a.BS ? (r - tok0) : a.BS);
-
-    const int l = a.layer0 + ll;
-    const int64_t row_bytes = static_cast<int64_t>(a.vec_per_row) * 16;
-    uint8_t *chunk_slab = a.chunk_base + static_cast<int64_t>(a.slot[c]) * a.slot_stride +
-                          ((static_cast<int64_t>(l) * 2 + kv) * r + tok0) * a.H * row_bytes;
-    vec16 *chunk_v = reinterpret_cast<vec16 *>(chunk_slab);
-    const int nvec = bs * a.H * a.vec_per_row;
-
-    const int32_t b = a.block_table[i * bpc + j];
-    if (b < 0 || b >= a.num_blocks) {
-        // A block id outside the cache: flag it, touch no cache byte, and on a store write
-        // zeros for the slab's chunk rows so that no stale staging or pool bytes (another
-        // request's state) are passed on as this chunk's contents.
-        if (threadIdx.x == 0)
-            __hip_atomic_store(a.err, KV_ASYNC_BAD_BLOCK, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        if (DIR == kPack) {
-            const vec16 zero = {0u, 0u, 0u, 0u};
-            for (int v = static_cast<int>(threadIdx.x); v < nvec; v += kThreads)
-                chunk_v[v] = zero;
-        }
-        return;
+    if (DIR == kPack) {
+        // Into mapped pinned host memory (zero-copy) the "nt sc1" policy moved 57.1 GB/s over the link
+        // against 55.7-55.9 with plain nontemporal stores (56.8 without either bit); into device memory
+        // plain nontemporal stores measured the same as any policy.
+        if constexpr (HOST_SIDE)
+            store16_nt_sc1(t.chunk, kTileVecs * 16, v, t.data);
+        else
+            store16(reinterpret_cast<vec16 *>(t.chunk) + v, t.data);
+    } else {
+        bool bad;
+        const int64_t off = block_offset(a, t, bad);
+        if (bad)
+            return;
+        if constexpr (WAVE)
+            store16_nt_sc1(t.cache + off, static_cast<int64_t>(a.slab_vecs) * 16, cache_vec(a, t.pos), t.data);
+        else
+            store16(reinterpret_cast<vec16 *>(t.cache + off) + cache_vec(a, t.pos), t.data);
     }
+}
 
-    const __amdgpu_buffer_rsrc_t chunk_buf = slab_buffer(chunk_slab, static_cast<int64_t>(nvec) * 16);
-    const int64_t slab_bytes = static_cast<int64_t>(a.H) * a.BS * row_bytes;
-    uint8_t *cache_slab = a.layer[ll] + static_cast<int64_t>(b) * a.block_stride + kv * slab_bytes;
-    vec16 *cache_v = reinterpret_cast<vec16 *>(cache_slab);
-    const __amdgpu_buffer_rsrc_t cache_buf = slab_buffer(cache_slab, slab_bytes);
-
-    const int tid = static_cast<int>(threadIdx.x);
-    if (a.nhd) {
-        // Token-major block: the slab's first bs*H rows are already in chunk row order.
-        if constexpr (DIR == kUnpack && !HOST_SIDE) {
-            // Device-side unpack: read the whole slab contiguously into the workgroup's reserved LDS,
-            // then write it with each pass spread over 8 segments of the slab (512 B each).  Paired
-            // on the paper's attention layout, this moved 3.0% more than the straight copy; 4, 16 or
-            // 32 segments measured the same as 8.  Host-side launches reserve no LDS.
-            constexpr int kSeg = 8, kPer = kThreads / kSeg;
-            if (nvec * 16 <= KVX_LDS_RESERVE && nvec % (kSeg * kPer) == 0) {
-                extern __shared__ vec16 lds_slab[];
-                for (int v = tid; v < nvec; v += kThreads)
-                    lds_slab[v] = load16(chunk_v + v);
-                __syncthreads();
-                const int seg = nvec / kSeg;
-                const int sg = tid / kPer, off = tid % kPer;
-                for (int i = 0; i * kPer < seg; ++i) {
-                    const int v = sg * seg + i * kPer + off;
-                    store16_cache(cache_buf, v, lds_slab[v]);
-                }
+// HOST_SIDE marks launches whose chunk side is mapped pinned host memory (zero-copy mode).
+template <int DIR, bool WAVE, bool HOST_SIDE>
+__global__ __launch_bounds__(kTileVecs) void gather_kernel(const GatherArgs a) {
+    if constexpr (!HOST_SIDE) {
+        // One workgroup per tile; the launch's last chunk may have fewer tiles.
+        if (static_cast<int>(blockIdx.z) == a.nchunks - 1 && static_cast<int>(blockIdx.x) >= a.last_tiles)
+            return;
+        Tile t;
+        start_tile<DIR, WAVE>(a, blockIdx.z, blockIdx.y, blockIdx.x, t);
+        finish_tile<DIR, WAVE, HOST_SIDE>(a, t);
+    } else {
+        // A capped grid strides over the tiles: the link, not the number of waves in flight, bounds
+        // these launches, and the CUs they leave free run other streams' kernels.  The next tile's reads
+        // are in flight while a tile is written.  Tiles are numbered over the chunks in order; only the
+        // launch's last chunk can have fewer per plane.
+        const int planes = 2 * a.nlayers;
+        const int full = (a.nchunks - 1) * planes * a.tiles;
+        const int total = full + planes * a.last_tiles;
+        auto start = [&](int id, Tile &t) {
+            int c = a.nchunks - 1, rest = id - full, per = a.last_tiles;
+            if (id < full) {
+                c = id / (planes * a.tiles);
+                rest = id - c * planes * a.tiles;
+                per = a.tiles;
+            }
+            const int plane = rest / per;
+            start_tile<DIR, WAVE>(a, c, plane, rest - plane * per, t);
+        };
+        // Two tiles in turn, by name: copying one to the other would wait for its reads.
+        Tile even, odd;
+        int id = blockIdx.x;  // the grid has at most `total` workgroups
+        start(id, even);
+        while (true) {
+            id += gridDim.x;
+            if (id >= total) {
+                finish_tile<DIR, WAVE, HOST_SIDE>(a, even);
                 return;
             }
+            start(id, odd);
+            finish_tile<DIR, WAVE, HOST_SIDE>(a, even);
+            id += gridDim.x;
+            if (id >= total) {
+                finish_tile<DIR, WAVE, HOST_SIDE>(a, odd);
+                return;
+            }
+            start(id, even);
+            finish_tile<DIR, WAVE, HOST_SIDE>(a, odd);
         }
-        for (int v = tid; v < nvec; v += kThreads) {
-            if (DIR == kPack)
-                store16_chunk<HOST_SIDE>(chunk_v, chunk_buf, v, load16(cache_v + v));
-            else
-                store16_cache(cache_buf, v, load16(chunk_v + v));
-        }
-        return;
-    }
-    RowWalker w(threadIdx.x, a.vec_per_row, a.H);
-    int base = 0;  // first chunk-side vector of the current tile (uniform across the workgroup)
-    // Full tiles: every thread has U in-range vectors; all U loads issue before any store.
-    for (; base + kThreads * U <= nvec; base += kThreads * U) {
-        const int v = base + tid;
-        int cache_off[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            cache_off[u] = w.cache_vec(a.BS);
-            w.advance();
-        }
-        vec16 buf[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (DIR == kPack)
-                buf[u] = load16(cache_v + cache_off[u]);
-            else
-                buf[u] = load16(chunk_v + v + u * kThreads);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (DIR == kPack)
-                store16_chunk<HOST_SIDE>(chunk_v, chunk_buf, v + u * kThreads, buf[u]);
-            else
-                store16_cache(cache_buf, cache_off[u], buf[u]);
-        }
-    }
-    // Tail: one vector at a time.
-    for (int v = base + tid; v < nvec; v += kThreads) {
-        const int co = w.cache_vec(a.BS);
-        w.advance();
-        if (DIR == kPack)
-            store16_chunk<HOST_SIDE>(chunk_v, chunk_buf, v, load16(cache_v + co));
-        else
-            store16_cache(cache_buf, co, load16(chunk_v + v));
     }
 }
-
-constexpr int kUnroll = KVX_UNROLL;
 
 }  // namespace
 
-int max_chunks_per_launch(const Geometry &g, int nlayers) {
-    const int64_t wgs_per_chunk = static_cast<int64_t>(nlayers) * 2 * g.blocks_per_chunk;
-    const int64_t max_wgs = (int64_t{1} << 31) / kThreads - 1;
-    int64_t m = max_wgs / wgs_per_chunk;
-    if (m > kMaxLaunchChunks)
-        m = kMaxLaunchChunks;
-    return static_cast<int>(m < 1 ? 1 : m);
+// Constants of divide() by d >= 1: shift = ceil(log2 d), mul = floor(2^(31 + shift) / d) + 1.
+static Divisor divisor(int64_t d) {
+    Divisor r{};
+    while ((int64_t{1} << r.shift) < d)
+        ++r.shift;
+    r.mul = static_cast<uint32_t>((uint64_t{1} << (31 + r.shift)) / static_cast<uint64_t>(d) + 1);
+    return r;
 }
 
-hipError_t launch_gather(const GatherArgs &args, Direction dir, bool host_side, hipStream_t stream) {
-    const int64_t slabs = static_cast<int64_t>(args.nchunks) * args.nlayers * 2 * args.blocks_per_chunk;
-    if (slabs <= 0)
-        return hipSuccess;
-    const int64_t host_wgs = dir == kPack ? KVX_HOST_WGS_PACK : KVX_HOST_WGS_UNPACK;
-    const int64_t grid = host_side && host_wgs > 0 ? std::min<int64_t>(slabs, host_wgs) : slabs;
-    const void *fn;
-    if (host_side)
-        fn = dir == kPack ? reinterpret_cast<const void *>(&gather_kernel<kPack, kUnroll, true>)
-                          : reinterpret_cast<const void *>(&gather_kernel<kUnpack, kUnroll, true>);
-    else
-        fn = dir == kPack ? reinterpret_cast<const void *>(&gather_kernel<kPack, kUnroll, false>)
-                          : reinterpret_cast<const void *>(&gather_kernel<kUnpack, kUnroll, false>);
-    // Device-side (staged) launches cap residency with reserved LDS; host-side launches are
-    // already few workgroups and reserve none.
-    const unsigned lds = host_side ? 0u : static_cast<unsigned>(KVX_LDS_RESERVE);
-    void *kargs[] = {const_cast<GatherArgs *>(&args)};
+template <bool HOST_SIDE>
+static const void *kernel_of(Direction dir, bool wave) {
+    if (wave)
+        return dir == kPack ? reinterpret_cast<const void *>(&gather_kernel<kPack, true, HOST_SIDE>)
+                            : reinterpret_cast<const void *>(&gather_kernel<kUnpack, true, HOST_SIDE>);
+    return dir == kPack ? reinterpret_cast<const void *>(&gather_kernel<kPack, false, HOST_SIDE>)
+                        : reinterpret_cast<const void *>(&gather_kernel<kUnpack, false, HOST_SIDE>);
+}
+
+// Launch over the chunks and layers that `a` names; what depends on the layout alone is set.
+static hipError_t launch(GatherArgs &a, Direction dir, bool host_side, hipStream_t stream) {
+    auto tiles_of = [&](int64_t r) { return (r * a.token_vecs + kTileVecs - 1) / kTileVecs; };
+    a.last_tiles = static_cast<int32_t>(tiles_of(a.last_r));
+    a.tiles = a.nchunks > 1 ? static_cast<int32_t>(tiles_of(a.C)) : a.last_tiles;
+    a.long_plane = static_cast<int64_t>(a.tiles) * kTileVecs > INT32_MAX;
+    dim3 grid(static_cast<uint32_t>(a.tiles), static_cast<uint32_t>(2 * a.nlayers), static_cast<uint32_t>(a.nchunks));
+    const bool wave = a.slab_vecs % 64 == 0;
+    if (host_side) {
+        const int64_t total = 2 * static_cast<int64_t>(a.nlayers) *
+                              ((a.nchunks - 1) * static_cast<int64_t>(a.tiles) + a.last_tiles);
+        const int64_t wgs = dir == kPack ? KVX_HOST_WGS_PACK
+                            : wave       ? KVX_HOST_WGS_UNPACK
+                                         : KVX_HOST_WGS_UNPACK_LANES;
+        grid = dim3(static_cast<uint32_t>(std::min(total, wgs)));
+    }
+    const void *fn = host_side ? kernel_of<true>(dir, wave) : kernel_of<false>(dir, wave);
+    const unsigned lds = host_side ? 0u : dir == kPack ? KVX_LDS_RESERVE_PACK : KVX_LDS_RESERVE_UNPACK;
+    void *kargs[] = {&a};
     // hipLaunchKernel reports launch failures directly (no sticky last-error state).
-    return hipLaunchKernel(fn, dim3(static_cast<uint32_t>(grid)), dim3(kThreads), kargs, lds, stream);
+    return hipLaunchKernel(fn, grid, dim3(kTileVecs), kargs, lds, stream);
+}
+
+hipError_t launch_gathers(const kv_cache *cache, const int32_t *block_table, int64_t n_tokens, Direction dir,
+                          int64_t chunk0, int nchunks, const int32_t *slots, uint8_t *chunk_base, int64_t slot_stride,
+                          bool host_side, int32_t *err, hipStream_t stream) {
+    const Geometry g = geometry(cache->layout, cache->block_stride_bytes);
+    GatherArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.chunk_base = chunk_base;
+    a.err = err;
+    a.slot_stride = slot_stride;
+    a.block_stride = g.block_stride;
+    a.num_blocks = cache->num_blocks;
+    a.C = static_cast<int32_t>(g.C);
+    a.blocks_per_chunk = static_cast<int32_t>(g.blocks_per_chunk);
+    a.H = static_cast<int32_t>(g.H);
+    a.BS = static_cast<int32_t>(g.BS);
+    a.vec_per_row = static_cast<int32_t>(g.vec_per_row);
+    a.token_vecs = a.H * a.vec_per_row;
+    a.slab_vecs = a.BS * a.token_vecs;
+    a.by_slab = divisor(a.slab_vecs);
+    a.by_row = divisor(a.vec_per_row);
+    a.by_head = divisor(a.H);
+    a.nhd = cache->block_order == KV_BLOCK_NHD ? 1 : 0;
+    for (int layer0 = 0; layer0 < g.L; layer0 += kMaxLaunchLayers) {
+        a.plane0 = 2 * layer0;
+        a.nlayers = static_cast<int>(std::min<int64_t>(kMaxLaunchLayers, g.L - layer0));
+        for (int l = 0; l < a.nlayers; ++l)
+            a.layer[l] = static_cast<uint8_t *>(cache->layer_ptrs[layer0 + l]);
+        for (int c0 = 0; c0 < nchunks; c0 += kMaxLaunchChunks) {
+            a.nchunks = std::min(kMaxLaunchChunks, nchunks - c0);
+            a.last_r = static_cast<int32_t>(std::min<int64_t>(g.C, n_tokens - (chunk0 + c0 + a.nchunks - 1) * g.C));
+            a.block_table = block_table + (chunk0 + c0) * g.blocks_per_chunk;
+            std::copy(slots + c0, slots + c0 + a.nchunks, a.slot);
+            const hipError_t e = launch(a, dir, host_side, stream);
+            if (e != hipSuccess)
+                return e;
+        }
+    }
+    return hipSuccess;
 }
 
 }  // namespace kvx

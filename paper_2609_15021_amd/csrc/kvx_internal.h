@@ -42,25 +42,35 @@ struct Geometry {
 
 Geometry geometry(const kv_layout &lay, int64_t block_stride_bytes);
 
+// Constants of a division of non-negative 31-bit numbers by a launch constant (kvx_gather.hip, divide()).
+struct Divisor {
+    uint32_t mul, shift;
+};
+
 // Kernel arguments of one gather (pack) or scatter (unpack) launch.  A launch covers
 // chunks [chunk0, chunk0 + nchunks) of the prefix and layers [layer0, layer0 + nlayers).
 // Passed by value so that every pointer and id is captured at enqueue time.
 struct GatherArgs {
-    uint8_t *layer[kMaxLaunchLayers];  // cache layer base pointers (device) of layers layer0..
+    // What every workgroup reads, in one run (scalar loads of up to 64 bytes).
     uint8_t *chunk_base;               // device-visible address of slot 0 (pool or staging)
-    const int32_t *block_table;        // device int32[ceil(n/BS)]
-    int32_t *err;                      // device-visible async error word
+    const int32_t *block_table;        // device int32[], from the launch's first block on
     int64_t slot_stride;               // bytes between slot ids at chunk_base
     int64_t block_stride;
-    int64_t n_tokens;                  // prefix length (for r_i of every chunk)
-    int64_t chunk0;                    // global index of the launch's first chunk
     int32_t num_blocks;
-    int32_t layer0, nlayers;
-    int32_t H, BS, C;
-    int32_t vec_per_row;
-    int32_t blocks_per_chunk;
+    int32_t plane0;                    // 2*layer0: the launch's first plane in a chunk
     int32_t nchunks;
+    int32_t C;
+    int32_t last_r;                    // tokens in the launch's last chunk
+    int32_t blocks_per_chunk;
+    int32_t token_vecs, slab_vecs;     // 16-byte vectors of one token of a plane, and of one block's K or V slab
+    int32_t H, BS, vec_per_row;
+    Divisor by_slab, by_row, by_head;  // division by slab_vecs, vec_per_row and H
     int32_t nhd;                       // cache blocks are [2][BS][H][D] (token-major)
+    int32_t long_plane;                // a plane's vectors do not fit 31 bits
+    int32_t tiles, last_tiles;         // tiles of a plane: of the launch's first chunk, of its last
+    int32_t nlayers;
+    int32_t *err;                      // device-visible async error word
+    uint8_t *layer[kMaxLaunchLayers];  // cache layer base pointers (device) of layers layer0..
     int32_t slot[kMaxLaunchChunks];    // slot id of each chunk of the launch
 };
 
@@ -84,16 +94,10 @@ struct StateArgs {
 hipError_t launch_state(const StateArgs &args, int64_t pieces, Direction dir, bool host_side,
                         hipStream_t stream);
 
-// Enqueue one launch on `stream`; host_side: the chunk side is mapped pinned host memory.
-// Returns the launch error (hipSuccess on success).
-hipError_t launch_gather(const GatherArgs &args, Direction dir, bool host_side, hipStream_t stream);
-
-// Largest chunk count per launch that keeps the grid within the 32-bit work-item limit.
-int max_chunks_per_launch(const Geometry &g, int nlayers);
-
 // Enqueue the pack/unpack launches for chunks [chunk0, chunk0 + nchunks) of a prefix of `cache`
-// (layers split over launches of at most kMaxLaunchLayers): slots[c] is the slot of chunk
-// chunk0 + c at chunk_base, slot_stride bytes apart.  No host allocation, no event.
+// (split over launches of at most kMaxLaunchLayers layers and kMaxLaunchChunks chunks): slots[c] is the slot of chunk
+// chunk0 + c at chunk_base, slot_stride bytes apart; host_side: chunk_base is mapped pinned host
+// memory.  Returns the first launch error.  No host allocation, no event.
 hipError_t launch_gathers(const kv_cache *cache, const int32_t *block_table, int64_t n_tokens, Direction dir,
                           int64_t chunk0, int nchunks, const int32_t *slots, uint8_t *chunk_base, int64_t slot_stride,
                           bool host_side, int32_t *err, hipStream_t stream);
