@@ -89,7 +89,10 @@ typedef int32_t kv_status;
 
 /* Host transfer modes (chosen explicitly; nothing is selected silently, cf. Sec. 3.2). */
 #define KV_MODE_ZERO_COPY 1u  /* gather/scatter kernels on `stream` access mapped pinned memory directly */
-#define KV_MODE_STAGED 2u     /* pack/unpack in device staging on `stream`; DMA copies on event-gated side streams */
+#define KV_MODE_STAGED 2u     /* pack/unpack in device staging on `stream`; DMA copies on event-gated side streams.
+                                 Requests of at most 32 MiB, or whose copies would average under 2 MiB, move as in
+                                 zero-copy mode instead (same result and ordering, a fraction of the time), unless
+                                 the pool was created with kv_pool_options.chunks_per_batch set */
 
 /* Pool memory kinds. */
 #define KV_HOST_COHERENT 0u     /* fine-grained pinned memory (default) */
@@ -137,7 +140,8 @@ typedef struct kv_pool_options {
                                   staging so kv_pool_set_mode can switch later */
     int32_t chunks_per_batch;  /* chunks per staging slot / per kernel launch, 1..256 (default 16
                                   staged and for a device pool, 256 zero-copy); applies to the mode
-                                  given here */
+                                  given here.  Set for a staged pool, it also keeps every staged
+                                  request on the DMA engines, short ones too */
     int32_t side_streams;      /* staged: DMA side streams per direction, 1..8 (default 1) */
     int32_t profile;           /* nonzero: time every pack/unpack launch (kv_pool_kernel_stats) */
     int64_t num_state_slots;   /* state-snapshot slots (0 = no state area) */
@@ -309,7 +313,7 @@ KV_API kv_status kv_load(const kv_cache *cache, const int32_t *block_table, int6
  * nothing: no hipMalloc/hipFree, no stream, no event, no host heap memory.  Each batch of
  * chunks is copied from the pool into the library's static device scratch of
  * KV_NOALLOC_SCRATCH_BYTES with hipMemcpyAsync and unpacked from there, every copy and kernel
- * on `stream` in order.  The first call on a device looks up that device's scratch address.
+ * on `stream` in order; short or fragmented requests move as KV_MODE_STAGED says of them.  The first call on a device looks up that device's scratch address.
  * Limits: KV_EUNSUPPORTED if one chunk (C*TB bytes) exceeds the scratch; KV_EINVAL for a
  * KV_POOL_DEVICE pool.  Every call on one GPU uses that GPU's one scratch array: calls that
  * overlap on one GPU (on two streams at once) race, and the caller must order them.

@@ -2,8 +2,8 @@
 // of pack/unpack kernels and DMA copies against the caller's stream.
 //
 // Ordering (the dependency whose omission the paper diagnoses, Sec. 3.2 and Fig. 2):
-//  * zero-copy mode: every kernel runs on the caller's stream, so it follows all earlier
-//    work on that stream and all later work follows it;
+//  * zero-copy mode, and staged requests that move directly (kvx::moves_directly): every kernel runs on
+//    the caller's stream, so it follows all earlier work on that stream and all later work follows it;
 //  * staged mode, store: pack kernels run on the caller's stream into staging slot k; the
 //    D2H copy of slot k runs on a side stream gated by an event recorded right after the
 //    pack; before exit the caller's stream waits for every side stream's last copy;
@@ -237,7 +237,15 @@ kv_status transfer(kv_pool *p, const kv_cache *cache, const int32_t *block_table
     const Geometry &g = p->geo;
     const int64_t nc = (n_tokens + g.C - 1) / g.C;
 
-    if (p->mode_of[dir] == KV_MODE_ZERO_COPY) {
+    bool direct = p->mode_of[dir] == KV_MODE_ZERO_COPY;
+    if (!direct) {
+        // Copies of the staged request: runs of consecutive slots within a batch.
+        int64_t copies = 0;
+        for (int64_t i = 0; i < nc; ++i)
+            copies += i % p->cpb == 0 || chunk_ids[i] != chunk_ids[i - 1] + 1;
+        direct = kvx::moves_directly(p, n_tokens * g.token_bytes, copies);
+    }
+    if (direct) {
         std::vector<int32_t> slots(static_cast<size_t>(nc));
         for (int64_t i = 0; i < nc; ++i)
             slots[static_cast<size_t>(i)] = static_cast<int32_t>(chunk_ids[i]);
@@ -343,7 +351,15 @@ kv_status enqueue_state(kv_pool *p, const kv_state *st, const StatePlan &plan, c
 kv_status transfer_state(kv_pool *p, const kv_state *st, const int64_t *pages, int64_t n, const int64_t *slot_ids,
                          hipStream_t stream, Direction dir) {
     const int64_t S = p->state_slot_bytes;
-    if (p->mode_of[dir] == KV_MODE_ZERO_COPY) {
+    bool direct = p->mode_of[dir] == KV_MODE_ZERO_COPY;
+    if (!direct) {
+        // Copies of the staged request: runs of consecutive slots (a full staging slot ends one too).
+        int64_t copies = n * S / (static_cast<int64_t>(p->cpb) * p->geo.slot_bytes);
+        for (int64_t k = 0; k < n; ++k)
+            copies += k == 0 || slot_ids[k] != slot_ids[k - 1] + 1;
+        direct = kvx::moves_directly(p, n * S, copies);
+    }
+    if (direct) {
         const StatePlan plan(st, n, kvx::kStatePiece);
         auto off = [&](int64_t k) { return slot_ids[k] * S; };
         return enqueue_state(p, st, plan, pages, 0, plan.pieces, p->dev_base + p->state_offset, off, !p->on_device,
@@ -530,6 +546,7 @@ kv_status kv_pool_create(const kv_layout *layout, int64_t num_slots, const kv_po
             p->host_kind = opts->host_kind;
             p->profile = opts->profile != 0;
             p->zc_chunks = zc_chunks;
+            p->dma_only = staged && opts->chunks_per_batch != 0;
 
             // On failure: free what was made, keeping the original error text.
             auto bail = [&](kv_status code) {

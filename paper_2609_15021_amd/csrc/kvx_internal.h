@@ -179,6 +179,7 @@ struct kv_pool {
     bool staging_contiguous = false;  // always false: staging is plain device memory
     Lane lane[2];                    // [kPack] stores, [kUnpack] loads
     int zc_chunks = 0;                 // chunks per zero-copy launch
+    bool dma_only = false;             // chunks_per_batch was given: no staged request moves directly
     // Last use of the pool on each caller stream (recorded after every store/load), so that
     // kv_pool_destroy never frees memory that queued kernels or copies still touch.
     std::vector<std::pair<hipStream_t, hipEvent_t>> last_use;
@@ -209,6 +210,21 @@ struct kv_pool {
 };
 
 namespace kvx {
+// Whether a staged request of `bytes` in `copies` DMA copies moves directly instead: by the zero-copy
+// kernels on the caller's stream.  Two kinds of request are better off so.
+//  * Short ones: the staged pipeline's kernel, event, cross-queue wait and copy cost about 65 us before and
+//    after the link's own time, a zero-copy kernel about 20 (store of 16 KiB: 85 us staged, 24 direct; 1 MiB:
+//    92 and 41; 16 MiB: 444 and 320; 32 MiB: 675 and 605; 128 MiB: 2,500 and 2,376).  Beyond 32 MiB (0.6 ms)
+//    the gain is under 10% and the kernels' hold on CUs lasts: a stream of large GEMMs beside a long
+//    zero-copy restore loses 30%, beside a staged one 0.5%.
+//  * Fragmented ones: a copy costs the DMA engine about 10 us however short (256 KiB: 18 GB/s, 1 MiB: 37,
+//    4 MiB: 50 of 57), so below 2 MiB a copy the link is idle for a quarter of the time or more.
+constexpr int64_t kDirectBytes = int64_t{32} << 20;
+constexpr int64_t kDirectCopyBytes = int64_t{2} << 20;
+inline bool moves_directly(const kv_pool *pool, int64_t bytes, int64_t copies) {
+    return !pool->dma_only && (bytes <= kDirectBytes || bytes / copies < kDirectCopyBytes);
+}
+
 // Make the pool's tier stream and block-table buffers (at least `table_bytes` each) if they are
 // missing or too small.  Caller holds pool->tier_mu and has made the pool's device current.
 kv_status tier_resources(kv_pool *pool, size_t table_bytes);

@@ -7,6 +7,9 @@
 // hipMalloc) get this variant: the staging is a file-scope device array, the copies and the unpack
 // kernels all run on the caller's stream in order, and no runtime object is created per call.
 //
+// Short and fragmented requests, where the copies' own cost is most of the time, are unpacked straight
+// from the mapped pool by the zero-copy kernels instead (kvx::moves_directly).
+//
 // The array's address differs per device.  It is looked up with hipGetSymbolAddress once per
 // device, with that device current, on the first call there, and only that address is ever
 // handed to copies and kernels: in host code the array's name is a host-side stand-in, not a
@@ -82,7 +85,22 @@ kv_status kv_load_noalloc(const kv_cache *cache, const int32_t *block_table, int
 
         hipStream_t s = static_cast<hipStream_t>(stream);
         const int64_t nc = (n_tokens + g.C - 1) / g.C;
-        const int per_batch = static_cast<int>(std::min<int64_t>(kScratchBytes / g.slot_bytes, kvx::kMaxLaunchChunks));
+        int64_t copies = 0;
+        const int64_t fit = std::min<int64_t>(kScratchBytes / g.slot_bytes, kvx::kMaxLaunchChunks);
+        for (int64_t i = 0; i < nc; ++i)
+            copies += i % fit == 0 || chunk_ids[i] != chunk_ids[i - 1] + 1;
+        if (kvx::moves_directly(pool, n_tokens * g.token_bytes, copies)) {
+            int32_t slots[kvx::kMaxLaunchChunks];
+            for (int64_t c0 = 0; c0 < nc; c0 += kvx::kMaxLaunchChunks) {
+                const int n = static_cast<int>(std::min<int64_t>(kvx::kMaxLaunchChunks, nc - c0));
+                for (int c = 0; c < n; ++c)
+                    slots[c] = static_cast<int32_t>(chunk_ids[c0 + c]);
+                KVX_HIP(kvx::launch_gathers(cache, block_table, n_tokens, kvx::kUnpack, c0, n, slots, pool->dev_base,
+                                            g.slot_bytes, true, pool->err_dev, s));
+            }
+            return KV_OK;
+        }
+        const int per_batch = static_cast<int>(fit);
         int32_t local[kvx::kMaxLaunchChunks];
         for (int c = 0; c < per_batch; ++c)
             local[c] = c;
