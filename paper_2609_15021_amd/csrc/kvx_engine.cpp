@@ -329,16 +329,17 @@ kv_status enqueue_state(kv_pool *p, const kv_state *st, const StatePlan &plan, c
         a.base = base;
         a.page_stride = plan.page_stride;
         a.page_bytes = plan.page_bytes;
-        a.piece = plan.piece;
-        a.q0 = q - k_first * per;
+        a.page0 = static_cast<int32_t>((q - k_first * per) / plan.ppp);
+        a.piece0 = static_cast<int32_t>(q % plan.ppp);
+        a.piece = static_cast<int32_t>(plan.piece);
+        a.npieces = static_cast<int32_t>(q_end - q);
         a.G = static_cast<int32_t>(plan.G);
         a.ppp = static_cast<int32_t>(plan.ppp);
-        a.nsnap = static_cast<int32_t>(k_last - k_first + 1);
         for (int64_t k = k_first; k <= k_last; ++k) {
             a.page[k - k_first] = pages[k];
             a.off[k - k_first] = snap_off(k);
         }
-        KVX_HIP(kvx::launch_state(a, q_end - q, dir, host_side, stream));
+        KVX_HIP(kvx::launch_state(a, dir, host_side, stream));
         q = q_end;
     }
     if (p->profile) {

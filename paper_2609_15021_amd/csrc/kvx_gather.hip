@@ -110,12 +110,6 @@ __device__ __forceinline__ void store16_nt_sc1(uint8_t *base, int64_t bytes, int
     __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, vec * 16, 0, kCachePolicyNtSc1);
 }
 
-// n / d for 0 <= n < 2^31 with the divisor's host-computed constants (Granlund and Montgomery, "Division
-// by Invariant Integers using Multiplication", PLDI 1994, Theorem 4.2 with N = 31).
-__device__ __forceinline__ int divide(int n, const Divisor &d) {
-    return static_cast<int>(__umulhi(static_cast<uint32_t>(n) << 1, d.mul) >> d.shift);
-}
-
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Block ids are read-only for the launch: the constant address space makes a uniform read a scalar load.
@@ -286,15 +280,6 @@ __global__ __launch_bounds__(kTileVecs) void gather_kernel(const GatherArgs a) {
 }
 
 }  // namespace
-
-// Constants of divide() by d >= 1: shift = ceil(log2 d), mul = floor(2^(31 + shift) / d) + 1.
-static Divisor divisor(int64_t d) {
-    Divisor r{};
-    while ((int64_t{1} << r.shift) < d)
-        ++r.shift;
-    r.mul = static_cast<uint32_t>((uint64_t{1} << (31 + r.shift)) / static_cast<uint64_t>(d) + 1);
-    return r;
-}
 
 template <bool HOST_SIDE>
 static const void *kernel_of(Direction dir, bool wave) {

@@ -22,10 +22,7 @@ constexpr int kMaxLaunchLayers = 64;   // layer pointers carried in one launch's
 constexpr int kMaxLaunchChunks = 256;  // slot ids carried in one launch's kernel arguments
 constexpr int kMaxStateLayers = 64;    // recurrent layers of a state snapshot (one launch carries all)
 constexpr int kMaxLaunchSnapshots = 128;  // snapshots carried in one state launch's arguments
-// Bytes of a page one workgroup moves (at most).  Paired on MI355X (48 x 3.06 MiB pages, device-side
-// launches, two orders): 16 KiB pieces moved 3.4-4.0% more on unpack than 64 KiB and the same as 32 KiB,
-// and pack followed (+5.5% over 64 KiB).
-constexpr int64_t kStatePiece = 16 * 1024;
+constexpr int64_t kStatePiece = 4 * 1024;  // bytes of a page one workgroup moves (kvx_state.hip)
 constexpr int64_t kMaxLaunchPieces = int64_t(1) << 22;  // workgroups of one state launch
 
 // Derived sizes of a layout (all bytes, 64-bit).
@@ -42,10 +39,24 @@ struct Geometry {
 
 Geometry geometry(const kv_layout &lay, int64_t block_stride_bytes);
 
-// Constants of a division of non-negative 31-bit numbers by a launch constant (kvx_gather.hip, divide()).
+// Division of 0 <= n < 2^31 by a launch constant d >= 1 as a multiplication: shift = ceil(log2 d), mul =
+// floor(2^(31 + shift) / d) + 1 (Granlund and Montgomery, "Division by Invariant Integers using
+// Multiplication", PLDI 1994, Theorem 4.2 with N = 31).
 struct Divisor {
     uint32_t mul, shift;
 };
+
+inline Divisor divisor(int64_t d) {
+    Divisor r{};
+    while ((int64_t{1} << r.shift) < d)
+        ++r.shift;
+    r.mul = static_cast<uint32_t>((uint64_t{1} << (31 + r.shift)) / static_cast<uint64_t>(d) + 1);
+    return r;
+}
+
+__device__ __forceinline__ int divide(int n, const Divisor &d) {
+    return static_cast<int>(__umulhi(static_cast<uint32_t>(n) << 1, d.mul) >> d.shift);
+}
 
 // Kernel arguments of one gather (pack) or scatter (unpack) launch.  A launch covers
 // chunks [chunk0, chunk0 + nchunks) of the prefix and layers [layer0, layer0 + nlayers).
@@ -76,23 +87,25 @@ struct GatherArgs {
 
 enum Direction { kPack = 0, kUnpack = 1 };
 
-// Kernel arguments of one state-snapshot launch.  Pages are cut into pieces of `piece`
-// bytes (the last piece of a page may be shorter); piece q of the launch is piece
-// j = q % ppp of layer g = (q / ppp) % G of snapshot k = q / (G*ppp).  The launch covers
-// pieces [q0, q0 + gridDim.x) of snapshots 0..nsnap-1 of its own lists.
+// Kernel arguments of one state-snapshot launch.  Pages are cut into ppp pieces of `piece` <=
+// kStatePiece bytes (the last piece of a page may be shorter).  The launch covers npieces <=
+// kMaxLaunchPieces pieces of its own lists of snapshots, from piece piece0 of page page0 on; page
+// p is layer p % G of snapshot p / G.
 struct StateArgs {
-    uint8_t *layer[kMaxStateLayers];   // device base of each recurrent layer's page buffer
     uint8_t *base;                     // device-visible packed side (state pool or staging)
-    int64_t page_stride, page_bytes, piece;
-    int64_t q0;
-    int64_t npieces;  // pieces in this launch (set by launch_state)
-    int32_t G, ppp, nsnap, pad;
+    int64_t page_stride, page_bytes;
+    int32_t page0, piece0, npieces, piece;
+    int32_t G, ppp;
+    int32_t last_piece, pad;           // bytes of a page's last piece (set by launch_state, as the next)
+    Divisor by_ppp, by_layers;         // division by ppp and G
+    uint8_t *layer[kMaxStateLayers];   // device base of each recurrent layer's page buffer
     int64_t page[kMaxLaunchSnapshots];  // device page id of each snapshot
     int64_t off[kMaxLaunchSnapshots];   // byte offset at `base` of each snapshot's packed bytes
 };
 
-hipError_t launch_state(const StateArgs &args, int64_t pieces, Direction dir, bool host_side,
-                        hipStream_t stream);
+// Enqueue one launch on `stream`; host_side: the packed side is mapped pinned host memory.  Returns the
+// launch error (hipSuccess on success).
+hipError_t launch_state(const StateArgs &args, Direction dir, bool host_side, hipStream_t stream);
 
 // Enqueue the pack/unpack launches for chunks [chunk0, chunk0 + nchunks) of a prefix of `cache`
 // (split over launches of at most kMaxLaunchLayers layers and kMaxLaunchChunks chunks): slots[c] is the slot of chunk

@@ -2,13 +2,16 @@
 // (convolution state, recurrent state and padding as opaque pages, Sec. 2.2) between
 // their device page buffers and the packed state slots, [G][page_bytes] per snapshot.
 //
-// Each page is contiguous on both sides, so the move is a batched copy: a workgroup moves
-// one piece (up to kStatePiece = 16 KiB) of one page at a time with 16-byte vectors.
-// Device-side launches run one workgroup per piece and pass it through LDS; host-side
-// (zero-copy) launches run a few workgroups that stride over the pieces and copy directly.
-// This work is bound by HBM (staging) or by
-// the host link (zero-copy); there is no arithmetic to put on the matrix cores.  Bytes
-// never pass through a float register.
+// Each page is contiguous on both sides, so the move is a batched copy: pages are cut into pieces of
+// 4 KiB (kStatePiece; the last one of a page may be shorter) and a workgroup moves one piece, one 16-byte
+// vector per lane.  Device-side launches run one workgroup per piece: HBM bounds them, and short pieces
+// keep neighbouring bytes in flight and every CU busy at any page size.  Measured on
+// MI355X against the earlier 16 KiB pieces through LDS, paired (store / load, TB/s read + written):
+// 8 x 48 pages of 3.06 MiB 5.88 -> 6.33 / 5.71 -> 6.29; one such snapshot 5.52 -> 5.79 / 5.29 -> 5.95;
+// 16 x 64 pages of 64 KiB 4.78 -> 5.32 / 4.60 -> 5.71; 64 x 64 pages of 8 KiB 3.45 -> 3.84 / 3.41 -> 4.07.
+// A residency cap, which gains the gather unpack, costs the load 1-2% here and the store 3-5%.
+// Host-side (zero-copy) launches run a few workgroups that stride over the pieces: the host link bounds
+// them.  There is no arithmetic to put on the matrix cores, and bytes never pass through a float register.
 #include <algorithm>
 
 #include "kvx_internal.h"
@@ -19,103 +22,91 @@ namespace {
 
 typedef uint32_t svec16 __attribute__((ext_vector_type(4)));
 
-// Vectors each lane keeps in flight before storing (host-side launches).
-constexpr int kStateUnroll = 4;
-// LDS of a device-side workgroup: the buffer the piece passes through, 32 KiB at a time.
-constexpr int kStateLds = 32768;
+static_assert(kStatePiece == kThreads * 16, "a piece is one vector per lane");
 
-// Workgroups of a host-side (zero-copy) launch, striding over its pieces (0: one per piece).
-// Measured on MI355X with 16 x 48 pages of 3.06 MiB (store / load GB/s): one per piece
-// 54.4 / 55.7, 8: 54.3 / 56.6, 16: 55.4 / 57.2, 32: 55.5 / 56.6, 64: 54.9 / 57.3.
-#ifndef KVX_STATE_HOST_WGS
-#define KVX_STATE_HOST_WGS 16
+// Workgroups of a host-side (zero-copy) launch, striding over its pieces with the next piece's reads in
+// flight, as the gather kernels' launches do.  48 pages of 3.06 MiB load at 57.0 GB/s with 16, 57.2 with 20,
+// 57.4 with 24 or 32; 16 x 36 pages of 8 KiB in 95, 94, 92 and 92 us.
+#ifndef KVX_STATE_HOST_WGS_PACK
+#define KVX_STATE_HOST_WGS_PACK 64
+#endif
+#ifndef KVX_STATE_HOST_WGS_UNPACK
+#define KVX_STATE_HOST_WGS_UNPACK 24
 #endif
 
-// Piece q of the launch's snapshots: [snapshot k][layer g][piece of the page].
-template <int DIR, bool HOST_SIDE>
-__device__ __forceinline__ void move_piece(const StateArgs &a, int64_t q) {
-    const int64_t per_snap = static_cast<int64_t>(a.G) * a.ppp;
-    const int k = static_cast<int>(q / per_snap);
-    const int64_t rem = q - k * per_snap;
-    const int g = static_cast<int>(rem / a.ppp);
-    const int64_t start = (rem - static_cast<int64_t>(g) * a.ppp) * a.piece;
-    const int64_t len = min(a.piece, a.page_bytes - start);
+// Cache-policy bits of buffer loads and stores, and descriptor word 3 of a raw (untyped) buffer.
+constexpr int kNt = 2, kSc1 = 16, kRawBuffer = 0x00020000;
 
+// A piece on its way, one vector per lane.
+struct Piece {
+    uint8_t *dst;
+    int bytes;
+    svec16 data;
+};
+
+// Start piece q of the launch (pieces run [snapshot k][layer g][piece of the page]): issue its reads.  The
+// buffer's range ends with the piece, so lanes beyond a short piece's end read zeros and write nothing: no
+// branch, no lane address, and so nothing that waits for an earlier piece's reads.
+template <int DIR>
+__device__ __forceinline__ void start_piece(const StateArgs &a, int q, Piece &p) {
+    const int t = a.piece0 + q, pages = divide(t, a.by_ppp);
+    const int page_id = a.page0 + pages;  // k*G + g
+    const int k = divide(page_id, a.by_layers), g = page_id - k * a.G;
+    const int j = t - pages * a.ppp;
+    const int64_t start = static_cast<int64_t>(j) * a.piece;
+    p.bytes = j == a.ppp - 1 ? a.last_piece : a.piece;
     uint8_t *page = a.layer[g] + a.page[k] * a.page_stride + start;
     uint8_t *packed = a.base + a.off[k] + static_cast<int64_t>(g) * a.page_bytes + start;
-    const svec16 *src = reinterpret_cast<const svec16 *>(DIR == kPack ? page : packed);
-    svec16 *dst = reinterpret_cast<svec16 *>(DIR == kPack ? packed : page);
-    const int nv = static_cast<int>(len >> 4);  // len <= piece <= kStatePiece
-    // Zero-copy stores into mapped pinned host memory use cache policy "nt sc1" (NT = 2, SC1 = 16),
-    // as the gather kernels' do: over the link it moved more than plain nontemporal stores.
-    const __amdgpu_buffer_rsrc_t dst_buf =
-        __builtin_amdgcn_make_buffer_rsrc(dst, 0, static_cast<int>(len), 0x00020000);
+    p.dst = DIR == kPack ? packed : page;
+    const __amdgpu_buffer_rsrc_t src =
+        __builtin_amdgcn_make_buffer_rsrc(DIR == kPack ? page : packed, 0, p.bytes, kRawBuffer);
+    p.data = __builtin_amdgcn_raw_buffer_load_b128(src, static_cast<int>(threadIdx.x) * 16, 0, kNt);
+}
 
-    if constexpr (!HOST_SIDE) {
-        // Device-side launches move the piece through LDS, at most 32 KiB at a time: contiguous
-        // reads into LDS, then writes with each pass spread over 8 segments of what LDS holds.
-        // Paired on 48 x 3.06 MiB pages (then in 64 KiB pieces), this moved 2.8-4.5% more (pack)
-        // and 3.9-4.0% more (unpack) than the direct copy with 4 vectors in flight; the LDS
-        // reservation alone changed nothing.
-        extern __shared__ svec16 lds_half[];
-        constexpr int kHalf = kStateLds / 16, kPer = kThreads / 8;
-        const int tid = static_cast<int>(threadIdx.x);
-        for (int h0 = 0; h0 < nv; h0 += kHalf) {
-            const int hn = min(kHalf, nv - h0);
-            if (hn % (8 * kPer) != 0) {  // a short tail: straight copy
-                for (int v = h0 + tid; v < h0 + hn; v += kThreads)
-                    __builtin_nontemporal_store(__builtin_nontemporal_load(src + v), dst + v);
-                continue;
-            }
-            for (int v = tid; v < hn; v += kThreads)
-                lds_half[v] = __builtin_nontemporal_load(src + h0 + v);
-            __syncthreads();
-            const int seg = hn / 8, sg = tid / kPer, off = tid % kPer;
-            for (int i = 0; i * kPer < seg; ++i) {
-                const int v = sg * seg + i * kPer + off;
-                __builtin_nontemporal_store(lds_half[v], dst + h0 + v);
-            }
-            __syncthreads();  // the next half overwrites the buffer
-        }
-        return;
-    }
-    for (int v0 = static_cast<int>(threadIdx.x); v0 < nv; v0 += kThreads * kStateUnroll) {
-        svec16 buf[kStateUnroll];
-#pragma unroll
-        for (int u = 0; u < kStateUnroll; ++u) {
-            const int v = v0 + u * kThreads;
-            if (v < nv)
-                buf[u] = __builtin_nontemporal_load(src + v);
-        }
-#pragma unroll
-        for (int u = 0; u < kStateUnroll; ++u) {
-            const int v = v0 + u * kThreads;
-            if (v < nv) {
-                if constexpr (HOST_SIDE && DIR == kPack)
-                    __builtin_amdgcn_raw_buffer_store_b128(buf[u], dst_buf, v * 16, 0, 2 | 16);
-                else
-                    __builtin_nontemporal_store(buf[u], dst + v);
-            }
-        }
-    }
+// Write a started piece to its place; "nt sc1" where the gather kernels' stores take it (into the mapped
+// pool and into the cache's pages).
+template <int DIR, bool HOST_SIDE>
+__device__ __forceinline__ void finish_piece(const Piece &p) {
+    const __amdgpu_buffer_rsrc_t dst = __builtin_amdgcn_make_buffer_rsrc(p.dst, 0, p.bytes, kRawBuffer);
+    __builtin_amdgcn_raw_buffer_store_b128(p.data, dst, static_cast<int>(threadIdx.x) * 16, 0,
+                                           DIR == kUnpack || HOST_SIDE ? kNt | kSc1 : kNt);
 }
 
 template <int DIR, bool HOST_SIDE>
 __global__ __launch_bounds__(kThreads) void state_kernel(const StateArgs a) {
-    if constexpr (HOST_SIDE) {
-        // A capped grid strides over the pieces: the link bounds these launches.
-        for (int64_t i = blockIdx.x; i < a.npieces; i += gridDim.x)
-            move_piece<DIR, HOST_SIDE>(a, a.q0 + i);
+    if constexpr (!HOST_SIDE) {
+        Piece p;
+        start_piece<DIR>(a, blockIdx.x, p);
+        finish_piece<DIR, HOST_SIDE>(p);
     } else {
-        move_piece<DIR, HOST_SIDE>(a, a.q0 + static_cast<int64_t>(blockIdx.x));  // one workgroup per piece
+        // Two pieces in turn, by name: copying one to the other would wait for its reads.
+        const int end = a.npieces, step = static_cast<int>(gridDim.x);
+        int q = static_cast<int>(blockIdx.x);  // the grid has at most npieces workgroups
+        Piece even, odd;
+        start_piece<DIR>(a, q, even);
+        while (true) {
+            q += step;
+            if (q >= end) {
+                finish_piece<DIR, HOST_SIDE>(even);
+                return;
+            }
+            start_piece<DIR>(a, q, odd);
+            finish_piece<DIR, HOST_SIDE>(even);
+            q += step;
+            if (q >= end) {
+                finish_piece<DIR, HOST_SIDE>(odd);
+                return;
+            }
+            start_piece<DIR>(a, q, even);
+            finish_piece<DIR, HOST_SIDE>(odd);
+        }
     }
 }
 
 }  // namespace
 
-hipError_t launch_state(const StateArgs &args, int64_t pieces, Direction dir, bool host_side,
-                        hipStream_t stream) {
-    if (pieces <= 0)
+hipError_t launch_state(const StateArgs &args, Direction dir, bool host_side, hipStream_t stream) {
+    if (args.npieces <= 0)
         return hipSuccess;
     const void *fn;
     if (host_side)
@@ -125,11 +116,13 @@ hipError_t launch_state(const StateArgs &args, int64_t pieces, Direction dir, bo
         fn = dir == kPack ? reinterpret_cast<const void *>(&state_kernel<kPack, false>)
                           : reinterpret_cast<const void *>(&state_kernel<kUnpack, false>);
     StateArgs a = args;
-    a.npieces = pieces;
-    const int64_t grid = host_side && KVX_STATE_HOST_WGS > 0 ? std::min<int64_t>(pieces, KVX_STATE_HOST_WGS) : pieces;
+    a.last_piece = static_cast<int32_t>(a.page_bytes - (a.ppp - 1) * static_cast<int64_t>(a.piece));
+    a.by_ppp = divisor(a.ppp);
+    a.by_layers = divisor(a.G);
+    const int wgs = dir == kPack ? KVX_STATE_HOST_WGS_PACK : KVX_STATE_HOST_WGS_UNPACK;
+    const int grid = host_side ? std::min(a.npieces, wgs) : a.npieces;
     void *kargs[] = {&a};
-    return hipLaunchKernel(fn, dim3(static_cast<uint32_t>(grid)), dim3(kThreads), kargs, host_side ? 0u : kStateLds,
-                           stream);
+    return hipLaunchKernel(fn, dim3(static_cast<uint32_t>(grid)), dim3(kThreads), kargs, 0, stream);
 }
 
 }  // namespace kvx

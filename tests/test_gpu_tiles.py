@@ -110,3 +110,49 @@ def _check(lay, order, where, n, bad):
     assert kvx.kv_pool_async_error(pool) == (kvx.KV_ASYNC_BAD_BLOCK if bad else 0)
     del view
     kvx.kv_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("where", ["zero_copy", "device", "staged"])
+@pytest.mark.parametrize("page", [16, 1008, 1024, 1040, 4080, 4096, 4112, 12304])
+def test_snapshot_piece_edges(page, where):
+    """Pages of one vector, next to a wave's 1 KiB and a piece's 4 KiB, and of several pieces; padded
+    pages, more snapshots than one launch carries.  (Staged: a staging slot of 2 KiB, under a piece.)"""
+    G, n, stride = 3, 130, page + 48
+    lay = Layout(1, 1, 16, 1, 8, 64)
+    rng = np.random.default_rng(harness.sub_seed("pieces", page))
+    A = rng.integers(0, 256, (G, n + 2, stride), dtype=np.uint8)
+    pages, slots = rng.permutation(n + 2)[:n], rng.permutation(n + 1)[:n]
+    want = np.full((n + 1) * G * page, POOL_SENT, dtype=np.uint8)
+    layers = [np.ascontiguousarray(A[g]).reshape(-1) for g in range(G)]
+    assert oracle.state_pack(layers, page, stride, pages, want, slots) == oracle.OK
+    back = [np.full((n + 2) * stride, CACHE_SENT, dtype=np.uint8) for _ in range(G)]
+    to = rng.permutation(n + 2)[:n]
+    assert oracle.state_unpack(back, page, stride, to, want, slots) == oracle.OK
+    area = dict(num_state_slots=n + 1, state_slot_bytes=G * page)
+    if where == "device":
+        pool = kvx.kv_pool_create(lay.kv, 1, "zero_copy", host_kind=kvx.KV_POOL_DEVICE, **area)
+        info = kvx.kv_pool_get_info(pool)
+
+        class View:
+            __cuda_array_interface__ = dict(shape=(want.size,), typestr="|u1", version=2,
+                                            data=(info["device_base"] + -(-info["pool_bytes"] // 4096) * 4096, False))
+        view = torch.as_tensor(View(), device=DEV)
+    else:
+        batch = 1 if where == "staged" else 0
+        pool = kvx.kv_pool_create(lay.kv, 1, where, chunks_per_batch=batch, **area)
+        view = torch.from_numpy(kvx.state_view(pool))
+    view.fill_(POOL_SENT)
+    dA = torch.from_numpy(A).to(DEV)
+    dB = torch.full_like(dA, CACHE_SENT)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    kvx.kv_store_state(kvx.State(dA, page, n + 2, stride), pages, pool, slots, s)
+    s.synchronize()
+    assert np.array_equal(view.cpu().numpy(), want), first_mismatch(view.cpu().numpy(), want)
+    kvx.kv_load_state(kvx.State(dB, page, n + 2, stride), to, pool, slots, s)
+    s.synchronize()
+    got = dB.cpu().numpy().reshape(G, -1)
+    for g in range(G):
+        assert np.array_equal(got[g], back[g]), f"layer {g}: " + first_mismatch(got[g], back[g])
+    del view
+    kvx.kv_pool_destroy(pool)
