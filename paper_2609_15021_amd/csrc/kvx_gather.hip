@@ -41,13 +41,6 @@ namespace {
 // One 16-byte vector as a native 128-bit register tuple (kept in VGPRs; never a float).
 typedef uint32_t vec16 __attribute__((ext_vector_type(4)));
 
-// Compile-time tuning knobs: streaming (nontemporal) access on the read and write side.
-#ifndef KVX_NT_LOAD
-#define KVX_NT_LOAD 1
-#endif
-#ifndef KVX_NT_STORE
-#define KVX_NT_STORE 1
-#endif
 // Dynamic LDS (unused) reserved per workgroup of a device-side unpack, to cap the workgroups resident per
 // CU: 26 KiB of the CU's 160 KiB allows 6 (24 waves).  Paired over twelve layouts, 6 unpacked
 // 1.4% more than 8 (the hardware's limit: 32 waves) and 0.4% more than 7, and 3-4% more on the 32 KiB slabs;
@@ -79,35 +72,29 @@ typedef uint32_t vec16 __attribute__((ext_vector_type(4)));
 #endif
 constexpr int kTileVecs = KVX_TILE_VECS;  // 16-byte vectors of a tile: one per lane of a workgroup
 
-__device__ __forceinline__ vec16 load16(const vec16 *p) {
-#if KVX_NT_LOAD
-    return __builtin_nontemporal_load(p);
-#else
-    return *p;
-#endif
-}
-
-__device__ __forceinline__ void store16(vec16 *p, vec16 v) {
-#if KVX_NT_STORE
-    __builtin_nontemporal_store(v, p);
-#else
-    *p = v;
-#endif
-}
-
-// Cache-side stores of unpack go through a buffer resource spanning the slab, with cache
-// policy "nt sc1" (nontemporal, agent scope).  Paired on six destination allocations of the
-// 27B-class layout, this moved 0.1-2.3% more than plain nontemporal stores on every one of
-// them (about 1% on average); "sc1" without "nt" varied by allocation, stores without either
-// lost 2-7%, and pack's stores and either kernel's loads gained nothing from other policies.
-constexpr int kCachePolicyNtSc1 = 2 | 16;  // CDNA3/4 cache-policy bits: NT = 2, SC1 = 16
+// Sides with a scalar base are read and written through buffer resources: one lane offset instead of a
+// lane address, and the hardware's range check in place of branches (beyond the range a read gives zeros
+// and a write does nothing).
+constexpr int kNt = 2, kSc1 = 16;            // CDNA3/4 cache-policy bits
 constexpr int kRawBufferFlags = 0x00020000;  // descriptor word 3 of a raw (untyped) buffer
 
-__device__ __forceinline__ void store16_nt_sc1(uint8_t *base, int64_t bytes, int vec, vec16 v) {
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(uint8_t *base, int bytes) {
     // bytes < 2^31: validation caps a block at 2 GiB, so a K or V slab at 1 GiB.
-    const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(base, 0, static_cast<int>(bytes), kRawBufferFlags);
-    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, vec * 16, 0, kCachePolicyNtSc1);
+    return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, kRawBufferFlags);
+}
+
+__device__ __forceinline__ vec16 load16(__amdgpu_buffer_rsrc_t from, int offset) {
+    return __builtin_amdgcn_raw_buffer_load_b128(from, offset, 0, kNt);
+}
+
+// NT_SC1: nontemporal at agent scope instead of plain nontemporal.  Paired on six destination allocations
+// of the 27B-class layout, unpack's cache-side stores moved 0.1-2.3% more with it on every one of them
+// ("sc1" without "nt" varied by allocation, stores without either lost 2-7%); pack's stores into mapped
+// pinned host memory 57.1 GB/s against 55.7-55.9 (56.8 without either bit); its stores into device memory
+// and either kernel's loads gained nothing from other policies than plain nontemporal.
+template <bool NT_SC1>
+__device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t to, int offset, vec16 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, to, offset, 0, NT_SC1 ? kNt | kSc1 : kNt);
 }
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -134,19 +121,24 @@ __device__ __forceinline__ int cache_vec(const GatherArgs &a, int p) {
     return ((row - s * a.H) * a.BS + s) * a.vec_per_row + (p - row * a.vec_per_row);
 }
 
-// Byte offset of the tile's block in the layer buffer.  bad: the id is outside the cache (flagged in the
-// pool's error word); the offset is then block 0's, so that a read through it stays in bounds.
-__device__ __forceinline__ int64_t block_offset(const GatherArgs &a, const Tile &t, bool &bad) {
-    bad = t.block < 0 || t.block >= a.num_blocks;
+// Whether the tile's block id is outside the cache (then flagged in the pool's error word).
+__device__ __forceinline__ bool bad_block(const GatherArgs &a, const Tile &t) {
+    const bool bad = t.block < 0 || t.block >= a.num_blocks;
     if (bad)
         __hip_atomic_store(a.err, KV_ASYNC_BAD_BLOCK, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    return bad ? 0 : t.block * a.block_stride;
+    return bad;
+}
+
+// The block's slab as a buffer; of no bytes if the id is outside the cache: no cache byte is then touched,
+// and pack's zeros keep stale staging or pool bytes (another request's state) out of the chunk.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_buffer(const GatherArgs &a, const Tile &t) {
+    const bool bad = bad_block(a, t);
+    return buffer(t.cache + (bad ? 0 : t.block * a.block_stride), bad ? 0 : a.slab_vecs * 16);
 }
 
 // Start tile x of plane `plane` (2*layer + kv) of launch chunk c, x < ceil(plane vectors / kTileVecs): find
-// its block and issue its reads.  Lanes beyond the plane's end read the tile's last vector again (no
-// branch around the load).  WAVE: a slab is a whole number of waves' vectors, so that a wave's 64 vectors
-// lie in one block and its table entry and cache base are scalars; otherwise each lane has its own.
+// its block and issue its reads.  WAVE: a slab is a whole number of waves' vectors, so that a wave's 64
+// vectors lie in one block and its table entry and cache base are scalars; otherwise each lane has its own.
 template <int DIR, bool WAVE>
 __device__ __forceinline__ void start_tile(const GatherArgs &a, int c, int plane, int x, Tile &t) {
     const int32_t slot = a.slot[c];
@@ -158,10 +150,12 @@ __device__ __forceinline__ void start_tile(const GatherArgs &a, int c, int plane
                  "s"(a.blocks_per_chunk), "s"(a.token_vecs), "s"(a.slab_vecs), "s"(a.H), "s"(a.BS),
                  "s"(a.vec_per_row), "s"(a.by_slab.mul), "s"(a.by_slab.shift), "s"(a.by_row.mul), "s"(a.by_row.shift),
                  "s"(a.by_head.mul), "s"(a.by_head.shift), "s"(a.nhd), "s"(a.long_plane));
-    const int r = c == a.nchunks - 1 ? a.last_r : a.C;  // tokens in the chunk
+    const bool last = c == a.nchunks - 1;
+    const int r = last ? a.last_r : a.C;  // tokens in the chunk
     const int64_t base = static_cast<int64_t>(x) * kTileVecs;
     const int64_t plane_vecs = static_cast<int64_t>(r) * a.token_vecs;
-    t.left = static_cast<int>(min(plane_vecs - base, static_cast<int64_t>(kTileVecs)));
+    const int tiles = last ? a.last_tiles : a.tiles;
+    t.left = x == tiles - 1 ? static_cast<int>(plane_vecs - base) : kTileVecs;
     // The tile's first block and the first vector inside its slab.
     int j0;
     if (a.long_plane) {
@@ -177,28 +171,30 @@ __device__ __forceinline__ void start_tile(const GatherArgs &a, int c, int plane
     t.cache = layer + (plane & 1) * (static_cast<int64_t>(a.slab_vecs) * 16);
     const TablePtr table = (TablePtr)(a.block_table + static_cast<int64_t>(c) * a.blocks_per_chunk + j0);
 
-    const int v = min(static_cast<int>(threadIdx.x), t.left - 1);
+    const int v = static_cast<int>(threadIdx.x);
+    // Unpack's reads do not wait for the block table.
     if (DIR == kUnpack)
-        t.data = load16(reinterpret_cast<const vec16 *>(t.chunk) + v);
+        t.data = load16(buffer(t.chunk, t.left * 16), v * 16);
     if constexpr (WAVE) {
-        // left is a multiple of 64 unless the last block is partial, and its wave then lies in that block.
-        const int wave = first + min(uniform(static_cast<int>(threadIdx.x) & ~63), (t.left - 1) & ~63);
+        // A wave beyond the tile's end takes the last block (its vectors are dropped).
+        const int wave = first + min(uniform(v & ~63), (t.left - 1) & ~63);
         const int j = divide(wave, a.by_slab);
         t.block = table[j];
         t.pos = wave - j * a.slab_vecs + (v & 63);
+        if (DIR == kPack)
+            t.data = load16(slab_buffer(a, t), cache_vec(a, t.pos) * 16);
     } else {
-        const int j = divide(first + v, a.by_slab);
+        const int inside = first + min(v, t.left - 1);
+        const int j = divide(inside, a.by_slab);
         t.block = table[j];
-        t.pos = first + v - j * a.slab_vecs;
-    }
-    if (DIR == kPack) {
-        bool bad;
-        const int64_t off = block_offset(a, t, bad);
-        t.data = load16(reinterpret_cast<const vec16 *>(t.cache + off) + cache_vec(a, t.pos));
-        // A block id outside the cache: no cache byte is passed on and the chunk gets zeros, not the stale
-        // staging or pool bytes of another request.
-        if (bad)
-            t.data = vec16{0u, 0u, 0u, 0u};
+        t.pos = inside - j * a.slab_vecs;
+        if (DIR == kPack) {
+            const bool bad = bad_block(a, t);
+            const uint8_t *slab = t.cache + (bad ? 0 : t.block * a.block_stride);  // bad: read block 0, pass on zeros
+            t.data = __builtin_nontemporal_load(reinterpret_cast<const vec16 *>(slab) + cache_vec(a, t.pos));
+            if (bad)
+                t.data = vec16{0u, 0u, 0u, 0u};
+        }
     }
 }
 
@@ -206,25 +202,13 @@ __device__ __forceinline__ void start_tile(const GatherArgs &a, int c, int plane
 template <int DIR, bool WAVE, bool HOST_SIDE>
 __device__ __forceinline__ void finish_tile(const GatherArgs &a, const Tile &t) {
     const int v = static_cast<int>(threadIdx.x);
-    if (v >= t.left)
-        return;
-    if (DIR == kPack) {
-        // Into mapped pinned host memory (zero-copy) the "nt sc1" policy moved 57.1 GB/s over the link
-        // against 55.7-55.9 with plain nontemporal stores (56.8 without either bit); into device memory
-        // plain nontemporal stores measured the same as any policy.
-        if constexpr (HOST_SIDE)
-            store16_nt_sc1(t.chunk, kTileVecs * 16, v, t.data);
-        else
-            store16(reinterpret_cast<vec16 *>(t.chunk) + v, t.data);
-    } else {
-        bool bad;
-        const int64_t off = block_offset(a, t, bad);
-        if (bad)
-            return;
-        if constexpr (WAVE)
-            store16_nt_sc1(t.cache + off, static_cast<int64_t>(a.slab_vecs) * 16, cache_vec(a, t.pos), t.data);
-        else
-            store16(reinterpret_cast<vec16 *>(t.cache + off) + cache_vec(a, t.pos), t.data);
+    if constexpr (DIR == kPack) {
+        store16<HOST_SIDE>(buffer(t.chunk, t.left * 16), v * 16, t.data);
+    } else if constexpr (WAVE) {
+        store16<true>(slab_buffer(a, t), v < t.left ? cache_vec(a, t.pos) * 16 : -1, t.data);
+    } else if (!bad_block(a, t) && v < t.left) {
+        vec16 *slab = reinterpret_cast<vec16 *>(t.cache + t.block * a.block_stride);
+        __builtin_nontemporal_store(t.data, slab + cache_vec(a, t.pos));
     }
 }
 
