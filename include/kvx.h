@@ -139,9 +139,10 @@ typedef struct kv_pool_options {
                                   each have their own ring); with mode zero-copy, > 0 also allocates
                                   staging so kv_pool_set_mode can switch later */
     int32_t chunks_per_batch;  /* chunks per staging slot / per kernel launch, 1..256 (default 16
-                                  staged and for a device pool, 256 zero-copy); applies to the mode
-                                  given here.  Set for a staged pool, it also keeps every staged
-                                  request on the DMA engines, short ones too */
+                                  staged, 256 zero-copy; for a device pool 16, more of small chunks
+                                  up to 1 GiB a launch); applies to the mode given here.  Set for
+                                  a staged pool, it also keeps every staged request on the DMA
+                                  engines, short ones too */
     int32_t side_streams;      /* staged: DMA side streams per direction, 1..8 (default 1) */
     int32_t profile;           /* nonzero: time every pack/unpack launch (kv_pool_kernel_stats) */
     int64_t num_state_slots;   /* state-snapshot slots (0 = no state area) */

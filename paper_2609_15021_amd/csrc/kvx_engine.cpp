@@ -30,6 +30,11 @@ namespace {
 
 constexpr int kDefaultStagingSlots = 3;
 constexpr int kDefaultChunksPerBatch = 16;
+// A device pool's launches take 16 chunks, more of small ones up to 1 GiB: a launch's start and end cost
+// about 4 us.  Loads of 128k tokens in 8 MiB chunks took 1,576 us in launches of 16, 1,366-1,515 of 128; a
+// 64 MiB prefix in 256 KiB chunks 61 us in launches of 16, 27 of 256 (stores 67 and 27); 49 and 64 MiB
+// chunks the same within placement from 16 to 64.
+constexpr int64_t kDeviceLaunchBytes = int64_t{1} << 30;
 // One DMA side stream per direction: a store and a load in flight at once then move ~99 GB/s in total
 // (two per direction measured 57-64 GB/s: the runtime spreads their copies over more copy engines).
 constexpr int kDefaultSideStreams = 1;
@@ -502,10 +507,12 @@ kv_status kv_pool_create(const kv_layout *layout, int64_t num_slots, const kv_po
         const bool staged = opts->mode == KV_MODE_STAGED;
         const int cpb = (staged && opts->chunks_per_batch) ? opts->chunks_per_batch : kDefaultChunksPerBatch;
         // Zero-copy launches into host memory default to the largest launch (they stride a capped grid);
-        // device-pool launches default to the staged launch shape (one workgroup per tile).
+        // device-pool launches default to up to kDeviceLaunchBytes.
+        const int64_t device_chunks =
+            std::max<int64_t>(kDefaultChunksPerBatch, kDeviceLaunchBytes / kvx::geometry(*layout, 0).slot_bytes);
         const int zc_chunks = (!staged && opts->chunks_per_batch) ? opts->chunks_per_batch
-                              : on_device                        ? kDefaultChunksPerBatch
-                                                                 : kvx::kMaxLaunchChunks;
+                              : on_device ? static_cast<int>(std::min<int64_t>(device_chunks, kvx::kMaxLaunchChunks))
+                                          : kvx::kMaxLaunchChunks;
         const bool want_staging = opts->mode == KV_MODE_STAGED || opts->staging_slots > 0;
         const int K = opts->staging_slots ? opts->staging_slots : kDefaultStagingSlots;
         if (want_staging && (K < 2 || K > 64))

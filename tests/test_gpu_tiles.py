@@ -156,3 +156,13 @@ def test_snapshot_piece_edges(page, where):
         assert np.array_equal(got[g], back[g]), f"layer {g}: " + first_mismatch(got[g], back[g])
     del view
     kvx.kv_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("nc", [255, 256, 257])
+def test_device_pool_launches_of_many_small_chunks(nc):
+    """A device pool takes up to 256 small chunks in one launch."""
+    lay = Layout(1, 1, 16, 1, 2, 4)
+    pool = kvx.kv_pool_create(lay.kv, 1, "zero_copy", host_kind=kvx.KV_POOL_DEVICE)
+    assert kvx.kv_pool_get_info(pool)["chunks_per_batch"] == 256
+    kvx.kv_pool_destroy(pool)
+    _check(lay, kvx.KV_BLOCK_HND, "device", nc * lay.C - 1, bad=True)
