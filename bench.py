@@ -1452,7 +1452,7 @@ def main():
         traffic, why = traffic_from_profile(dom)
         roof = {"bound": "hbm", "achieved": kd[dom]["achieved_GBps"], "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                 "frac": kd[dom]["frac_of_hbm_peak"], "traffic": traffic,
-                "kernel": f"gather_kernel<{dom}> (device-only leg: one workgroup per 32 KiB slab, 16 chunks per "
+                "kernel": f"gather_kernel<{dom}> (device-only leg: one workgroup per 4 KiB tile, 16 chunks per "
                           "launch, live HIP events on the launch stream)",
                 "launches": kd[dom]["launches"], "avg_launch_ms": kd[dom]["avg_launch_ms"],
                 "algorithmic_bytes_per_launch": kd[dom]["algorithmic_bytes_per_launch"],
