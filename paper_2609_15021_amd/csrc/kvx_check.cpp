@@ -64,10 +64,16 @@ kv_status check_layout(const kv_layout &lay) {
                     static_cast<long long>(row));
     // Slabs (one block's K or V) are addressed with signed 32-bit byte offsets: at most 2 GiB
     // per block.
-    const int64_t block_bytes = 2LL * lay.num_kv_heads * lay.block_size * row;
-    if (block_bytes > (int64_t{1} << 31))
-        return fail(KV_EUNSUPPORTED, "block of %lld bytes is too large (at most 2 GiB)",
-                    static_cast<long long>(block_bytes));
+    const unsigned __int128 block_bytes =
+        static_cast<unsigned __int128>(2) * lay.num_kv_heads * lay.block_size * static_cast<uint64_t>(row);
+    if (block_bytes > (uint64_t{1} << 31))
+        return fail(KV_EUNSUPPORTED, "block of %.0f bytes is too large (at most 2 GiB)",
+                    static_cast<double>(block_bytes));
+    // Every size derived from a layout (up to a chunk's C*TB bytes) fits 64 bits.
+    const unsigned __int128 chunk_bytes =
+        block_bytes * static_cast<uint64_t>(lay.chunk_tokens / lay.block_size) * static_cast<uint64_t>(lay.num_layers);
+    if (chunk_bytes > INT64_MAX)
+        return fail(KV_EINVAL, "chunk of %d tokens in %d layers overflows 64 bits", lay.chunk_tokens, lay.num_layers);
     return KV_OK;
 }
 

@@ -508,11 +508,12 @@ kv_status kv_pool_create(const kv_layout *layout, int64_t num_slots, const kv_po
         const int cpb = (staged && opts->chunks_per_batch) ? opts->chunks_per_batch : kDefaultChunksPerBatch;
         // Zero-copy launches into host memory default to the largest launch (they stride a capped grid);
         // device-pool launches default to up to kDeviceLaunchBytes.
-        const int64_t device_chunks =
-            std::max<int64_t>(kDefaultChunksPerBatch, kDeviceLaunchBytes / kvx::geometry(*layout, 0).slot_bytes);
-        const int zc_chunks = (!staged && opts->chunks_per_batch) ? opts->chunks_per_batch
-                              : on_device ? static_cast<int>(std::min<int64_t>(device_chunks, kvx::kMaxLaunchChunks))
-                                          : kvx::kMaxLaunchChunks;
+        int zc_chunks = kvx::kMaxLaunchChunks;
+        if (!staged && opts->chunks_per_batch)
+            zc_chunks = opts->chunks_per_batch;
+        else if (on_device)  // check_layout has bounded the chunk: its bytes are positive
+            zc_chunks = static_cast<int>(std::clamp<int64_t>(kDeviceLaunchBytes / kvx::geometry(*layout, 0).slot_bytes,
+                                                             kDefaultChunksPerBatch, kvx::kMaxLaunchChunks));
         const bool want_staging = opts->mode == KV_MODE_STAGED || opts->staging_slots > 0;
         const int K = opts->staging_slots ? opts->staging_slots : kDefaultStagingSlots;
         if (want_staging && (K < 2 || K > 64))

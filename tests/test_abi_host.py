@@ -4,6 +4,7 @@ import ctypes
 import os
 import re
 import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -126,6 +127,34 @@ def test_kv_check_agrees_with_oracle_validation():
         assert (got == kvx.KV_OK) == (want == oracle.OK), (L, H, D, E, BS, C, n, slots, ids, store, got)
         agree += 1
     assert agree > 100
+
+
+# 8 layers of 2 GiB one-token blocks; one chunk of 2^30 of them is 2^64 bytes, which wraps to 0.  The next wraps to
+# 16 GiB, the one after to a negative size, and in the last the block wraps to 0 too.
+WRAPPING_LAYOUTS = [(8, 1 << 15, 1 << 13, 4, 1, 1 << 30), (8, 1 << 15, 1 << 13, 4, 1, (1 << 30) + 1),
+                    (4, 1 << 15, 1 << 13, 4, 1, (1 << 31) - 1), (1, 1 << 30, 16, 1, 1 << 30, 1 << 30)]
+
+
+@pytest.mark.parametrize("dims", WRAPPING_LAYOUTS)
+def test_layouts_beyond_64_bits_are_refused(dims):
+    """A chunk of 2^63 bytes or more is an error status for every pool kind, before any HIP call, and for kv_check.
+    (The pools are asked for in a process of their own, whose end is seen here.)"""
+    from paper_2609_15021_amd import kvx
+    lay = kvx.make_layout(*dims)
+    assert _check(kvx, _fake_cache(kvx, lay, 2), lay, 2, 10, [0], True) in (kvx.KV_EINVAL, kvx.KV_EUNSUPPORTED)
+    assert "bytes" in kvx.kv_last_error() or "64 bits" in kvx.kv_last_error()
+    code = f"""
+from paper_2609_15021_amd import kvx
+for mode, kind in (("staged", kvx.KV_HOST_COHERENT), ("zero_copy", kvx.KV_HOST_COHERENT),
+                   ("zero_copy", kvx.KV_POOL_DEVICE)):
+    try:
+        kvx.kv_pool_create(kvx.make_layout(*{dims}), 1, mode, host_kind=kind)
+    except kvx.KvError as e:
+        print(e.status)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, (r.returncode, r.stderr)
+    assert set(r.stdout.split()) <= {str(kvx.KV_EINVAL), str(kvx.KV_EUNSUPPORTED)} and len(r.stdout.split()) == 3, r.stdout
 
 
 def _fake_state(kvx, G, page_bytes, num_pages, stride=0, align=16, ptr_base=0x7E0000000000):
