@@ -157,15 +157,7 @@ __device__ __forceinline__ void start_tile(const GatherArgs &a, int c, int plane
     const int tiles = last ? a.last_tiles : a.tiles;
     t.left = x == tiles - 1 ? static_cast<int>(plane_vecs - base) : kTileVecs;
     // The tile's first block and the first vector inside its slab.
-    int j0;
-    if (a.long_plane) {
-        // Beyond divide()'s range: a rounded quotient, one too large at most.
-        j0 = uniform(static_cast<int>(static_cast<double>(base) / a.slab_vecs));
-        if (static_cast<int64_t>(j0) * a.slab_vecs > base)
-            --j0;
-    } else {
-        j0 = divide(static_cast<int>(base), a.by_slab);
-    }
+    const int j0 = a.long_plane ? uniform(divide_long(base, a.slab_vecs)) : divide(static_cast<int>(base), a.by_slab);
     const int first = static_cast<int>(base - static_cast<int64_t>(j0) * a.slab_vecs);
     t.chunk = a.chunk_base + slot * a.slot_stride + ((a.plane0 + plane) * plane_vecs + base) * 16;
     t.cache = layer + (plane & 1) * (static_cast<int64_t>(a.slab_vecs) * 16);

@@ -54,8 +54,16 @@ inline Divisor divisor(int64_t d) {
     return r;
 }
 
-__device__ __forceinline__ int divide(int n, const Divisor &d) {
-    return static_cast<int>(__umulhi(static_cast<uint32_t>(n) << 1, d.mul) >> d.shift);
+__host__ __device__ __forceinline__ int divide(int n, const Divisor &d) {
+    const uint64_t high = static_cast<uint64_t>(static_cast<uint32_t>(n) << 1) * d.mul >> 32;
+    return static_cast<int>(static_cast<uint32_t>(high) >> d.shift);
+}
+
+// floor(n / d) beyond divide()'s range, for 0 <= n < 2^53, d >= 1 and a quotient below 2^31.  n / d is at least 1 / d
+// below the next whole number q, and the nearest double would be q only if half the spacing there, at most
+// q * 2^-53, reached 1 / d: not while q * d <= 2^53.
+__host__ __device__ __forceinline__ int divide_long(int64_t n, int d) {
+    return static_cast<int>(static_cast<double>(n) / d);
 }
 
 // Kernel arguments of one gather (pack) or scatter (unpack) launch.  A launch covers
