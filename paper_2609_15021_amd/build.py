@@ -17,6 +17,7 @@ HARNESS = os.path.join(ROOT, "harness")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
 LIB_KVX = os.path.join(PKG, "libkvx.so")
+LIB_LIMITS = os.path.join(ROOT, "tests", "native", "libkvx_limits.so")
 LIB_HARNESS = os.path.join(HARNESS, "libkvx_harness.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -54,6 +55,9 @@ def _compile_objs(sources, src_dir, tag, extra, verbose):
     return objs
 
 
+KVX_FLAGS = ["-I", INCLUDE, "-I", CSRC, "-fvisibility=hidden"]
+
+
 def _link(objs, out, verbose):
     tmp = out + ".tmp"
     _run([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
@@ -61,8 +65,13 @@ def _link(objs, out, verbose):
 
 
 def build_kvx(verbose: bool = False) -> str:
-    objs = _compile_objs(KVX_SOURCES, CSRC, "kvx", ["-I", INCLUDE, "-I", CSRC, "-fvisibility=hidden"], verbose)
+    objs = _compile_objs(KVX_SOURCES, CSRC, "kvx", KVX_FLAGS, verbose)
     _link(objs, LIB_KVX, verbose)
+    # The tests' build of the same library: planes of any size go the ways of the largest, which no memory here
+    # holds twice (block ids beyond the 31-bit division; planes of over 3 tiles beyond one launch dimension).
+    limits = _compile_objs(["kvx_gather.hip"], CSRC, "limits",
+                           [*KVX_FLAGS, "-DKVX_DIVIDE_VECS=0", "-DKVX_GRID_TILES=3"], verbose)
+    _link([o for o in objs if not o.endswith("kvx_kvx_gather.o")] + limits, LIB_LIMITS, verbose)
     return LIB_KVX
 
 

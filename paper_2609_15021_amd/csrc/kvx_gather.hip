@@ -71,6 +71,17 @@ typedef uint32_t vec16 __attribute__((ext_vector_type(4)));
 #define KVX_TILE_VECS 256
 #endif
 constexpr int kTileVecs = KVX_TILE_VECS;  // 16-byte vectors of a tile: one per lane of a workgroup
+// Vectors of a plane up to which its blocks are found with divide(), whose range ends there (32 GiB).  A test
+// build sets 0, so that small planes go the way of the longest.
+#ifndef KVX_DIVIDE_VECS
+#define KVX_DIVIDE_VECS INT32_MAX
+#endif
+// Tiles of a plane that one launch dimension takes as workgroups: a dimension holds fewer than 2^32 work-items.
+// Longer planes (64 GiB) run the strided kernel on a grid that fills the chip.
+#ifndef KVX_GRID_TILES
+#define KVX_GRID_TILES ((int64_t{1} << 32) / kTileVecs - 1)
+#endif
+constexpr int64_t kStridedDeviceWgs = 2048;  // 8 per CU
 
 // Sides with a scalar base are read and written through buffer resources: one lane offset instead of a
 // lane address, and the hardware's range check in place of branches (beyond the range a read gives zeros
@@ -271,18 +282,19 @@ static hipError_t launch(GatherArgs &a, Direction dir, bool host_side, hipStream
     auto tiles_of = [&](int64_t r) { return (r * a.token_vecs + kTileVecs - 1) / kTileVecs; };
     a.last_tiles = static_cast<int32_t>(tiles_of(a.last_r));
     a.tiles = a.nchunks > 1 ? static_cast<int32_t>(tiles_of(a.C)) : a.last_tiles;
-    a.long_plane = static_cast<int64_t>(a.tiles) * kTileVecs > INT32_MAX;
+    a.long_plane = static_cast<int64_t>(a.tiles) * kTileVecs > KVX_DIVIDE_VECS;
     dim3 grid(static_cast<uint32_t>(a.tiles), static_cast<uint32_t>(2 * a.nlayers), static_cast<uint32_t>(a.nchunks));
-    const bool wave = a.slab_vecs % 64 == 0;
-    if (host_side) {
+    const bool wave = a.slab_vecs % 64 == 0, strided = host_side || a.tiles > KVX_GRID_TILES;
+    if (strided) {
         const int64_t total = 2 * static_cast<int64_t>(a.nlayers) *
                               ((a.nchunks - 1) * static_cast<int64_t>(a.tiles) + a.last_tiles);
-        const int64_t wgs = dir == kPack ? KVX_HOST_WGS_PACK
-                            : wave       ? KVX_HOST_WGS_UNPACK
-                                         : KVX_HOST_WGS_UNPACK_LANES;
+        const int64_t wgs = !host_side     ? kStridedDeviceWgs
+                            : dir == kPack ? KVX_HOST_WGS_PACK
+                            : wave         ? KVX_HOST_WGS_UNPACK
+                                           : KVX_HOST_WGS_UNPACK_LANES;
         grid = dim3(static_cast<uint32_t>(std::min(total, wgs)));
     }
-    const void *fn = host_side ? kernel_of<true>(dir, wave) : kernel_of<false>(dir, wave);
+    const void *fn = strided ? kernel_of<true>(dir, wave) : kernel_of<false>(dir, wave);
     const unsigned lds = host_side ? 0u : dir == kPack ? KVX_LDS_RESERVE_PACK : KVX_LDS_RESERVE_UNPACK;
     void *kargs[] = {&a};
     // hipLaunchKernel reports launch failures directly (no sticky last-error state).

@@ -99,10 +99,10 @@ class KvError(RuntimeError):
         self.status = status
 
 
-def _open():
-    if not os.path.exists(LIB_PATH):
-        raise ImportError(f"kvx HIP library not built ({LIB_PATH} missing); run __graft_entry__.build()")
-    lib = ctypes.CDLL(LIB_PATH)
+def _open(path=LIB_PATH):
+    if not os.path.exists(path):
+        raise ImportError(f"kvx HIP library not built ({path} missing); run __graft_entry__.build()")
+    lib = ctypes.CDLL(path)
     P, i32, i64, u32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint32
     sig = {
         "kv_pool_create": ([ctypes.POINTER(KvLayout), i64, ctypes.POINTER(KvPoolOptions), ctypes.POINTER(P)], i32),

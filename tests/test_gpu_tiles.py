@@ -8,7 +8,7 @@ import torch
 
 import harness
 import oracle
-from paper_2609_15021_amd import kvx
+from paper_2609_15021_amd import build, kvx
 from tests.gpu_support import DEV, Layout, bt_tensor, first_mismatch
 
 pytestmark = pytest.mark.gpu
@@ -110,6 +110,21 @@ def _check(lay, order, where, n, bad):
     assert kvx.kv_pool_async_error(pool) == (kvx.KV_ASYNC_BAD_BLOCK if bad else 0)
     del view
     kvx.kv_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("where", ["zero_copy", "device"])
+@pytest.mark.parametrize("order", [kvx.KV_BLOCK_HND, kvx.KV_BLOCK_NHD])
+@pytest.mark.parametrize("name", LAYOUTS)
+def test_planes_beyond_the_limits_of_a_launch(name, order, where, monkeypatch):
+    """A build of the library in which planes of any size find their blocks as those of 32 GiB and more do, and
+    planes of more than 3 tiles are launched as those of 64 GiB and more are."""
+    monkeypatch.setattr(kvx, "_lib", kvx._open(build.LIB_LIMITS))
+    lay = Layout(*LAYOUTS[name])
+    plane = lay.H * lay.D * lay.E * lay.C
+    for n in (1, lay.C, 2 * lay.C + 1, 3 * lay.C - 1):
+        print(f"[limits] {name} order={order} {where} n={n} tiles={-(-plane // 4096)}", flush=True)
+        _check(lay, order, where, n, bad=False)
+    _check(lay, order, where, 2 * lay.C + lay.BS, bad=True)
 
 
 @pytest.mark.parametrize("where", ["zero_copy", "device", "staged"])
