@@ -87,12 +87,14 @@ typedef int32_t kv_status;
 #define KV_EASYNC (-5)        /* a device-side check failed in an earlier call (kv_pool_async_error) */
 #define KV_EBUSY (-6)         /* pool index: no slot can be freed (every slot is pinned or pending) */
 
-/* Host transfer modes (chosen explicitly; nothing is selected silently, cf. Sec. 3.2). */
+/* Host transfer modes (chosen explicitly and reported in kv_pool_info, cf. Sec. 3.2). */
 #define KV_MODE_ZERO_COPY 1u  /* gather/scatter kernels on `stream` access mapped pinned memory directly */
 #define KV_MODE_STAGED 2u     /* pack/unpack in device staging on `stream`; DMA copies on event-gated side streams.
-                                 Requests of at most 32 MiB, or whose copies would average under 2 MiB, move as in
-                                 zero-copy mode instead (same result and ordering, a fraction of the time), unless
-                                 the pool was created with kv_pool_options.chunks_per_batch set */
+                                 Part of the mode: requests of at most 32 MiB, or whose copies would average under
+                                 2 MiB, move by the zero-copy kernels instead.  Result and ordering are the same
+                                 and the request is faster on an idle GPU, but it takes CUs from other streams'
+                                 work meanwhile, as zero-copy mode does */
+#define KV_MODE_STAGED_DMA 3u /* staged, with every request on the DMA engines, short and fragmented ones too */
 
 /* Pool memory kinds. */
 #define KV_HOST_COHERENT 0u     /* fine-grained pinned memory (default) */
@@ -133,16 +135,17 @@ typedef struct kv_cache {
 
 /* Pool creation options.  Zero-initialised fields take the documented defaults. */
 typedef struct kv_pool_options {
-    uint32_t mode;             /* KV_MODE_ZERO_COPY or KV_MODE_STAGED (required, no default) */
+    uint32_t mode;             /* KV_MODE_ZERO_COPY, KV_MODE_STAGED or KV_MODE_STAGED_DMA (required, no
+                                  default) */
     uint32_t host_kind;        /* KV_HOST_COHERENT (0), KV_HOST_NONCOHERENT or KV_POOL_DEVICE */
     int32_t staging_slots;     /* staged ring depth K >= 2 per direction (default 3; stores and loads
                                   each have their own ring); with mode zero-copy, > 0 also allocates
                                   staging so kv_pool_set_mode can switch later */
     int32_t chunks_per_batch;  /* chunks per staging slot / per kernel launch, 1..256 (default 16
                                   staged, 256 zero-copy; for a device pool 16, more of small chunks
-                                  up to 1 GiB a launch); applies to the mode given here.  Set for
-                                  a staged pool, it also keeps every staged request on the DMA
-                                  engines, short ones too */
+                                  up to 1 GiB a launch); applies to the mode given here.  Set, it
+                                  also keeps every staged request and kv_load_noalloc on the DMA
+                                  engines, as KV_MODE_STAGED_DMA does */
     int32_t side_streams;      /* staged: DMA side streams per direction, 1..8 (default 1) */
     int32_t profile;           /* nonzero: time every pack/unpack launch (kv_pool_kernel_stats) */
     int64_t num_state_slots;   /* state-snapshot slots (0 = no state area) */
@@ -173,7 +176,8 @@ typedef struct kv_pool_info {
     void *state_host_base;     /* host address of state slot 0 (NULL without a state area); the
                                   state area follows the chunk slots in the same pinned region */
     uint32_t load_mode;        /* mode of loads; `mode` above is the mode of stores */
-    uint32_t pad;
+    uint32_t direct_bytes;     /* KV_MODE_STAGED requests of at most this many bytes move by the zero-copy
+                                  kernels, whatever their copies; 0 if none do (chunks_per_batch was set) */
 } kv_pool_info;
 
 /* A replica's recurrent-state page buffers (hybrid models).  The caller owns all memory. */
@@ -234,9 +238,9 @@ KV_API int64_t kv_pool_num_slots(const kv_pool *pool);
 
 /* Switch mode between calls, for stores and loads alike.  The transfer path is chosen by the
  * pool's owner and reported in kv_pool_info, never selected silently (Sec. 3.2: a CLI default
- * selected the allocator whose raw-pointer fallback dropped the stream dependency).  Both modes
- * keep the ordering contract.  Affects calls made after it returns; calls already enqueued keep
- * their mode.  KV_EINVAL for a NULL pool, an unknown mode or staged mode without staging. */
+ * selected the allocator whose raw-pointer fallback dropped the stream dependency).  Every mode
+ * keeps the ordering contract.  Affects calls made after it returns; calls already enqueued keep
+ * their mode.  KV_EINVAL for a NULL pool, an unknown mode or a staged mode without staging. */
 KV_API kv_status kv_pool_set_mode(kv_pool *pool, uint32_t mode);
 
 /* Switch mode between calls, separately for stores and loads (e.g. a tier that stores staged and
@@ -311,11 +315,13 @@ KV_API kv_status kv_load(const kv_cache *cache, const int32_t *block_table, int6
 /*
  * kv_load_noalloc -- kv_load for callers that cannot allocate: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, result, ordering
- * contract and argument errors as kv_load, for a host pool in either mode.  It allocates
+ * contract and argument errors as kv_load, for a host pool in any mode.  It allocates
  * nothing: no hipMalloc/hipFree, no stream, no event, no host heap memory.  Each batch of
  * chunks is copied from the pool into the library's static device scratch of
  * KV_NOALLOC_SCRATCH_BYTES with hipMemcpyAsync and unpacked from there, every copy and kernel
- * on `stream` in order; short or fragmented requests move as KV_MODE_STAGED says of them.  The first call on a device looks up that device's scratch address.
+ * on `stream` in order.  The requests that KV_MODE_STAGED moves by the zero-copy kernels are moved
+ * by them here too, unless loads are in KV_MODE_STAGED_DMA or the pool was created with
+ * chunks_per_batch set.  The first call on a device looks up that device's scratch address.
  * Limits: KV_EUNSUPPORTED if one chunk (C*TB bytes) exceeds the scratch; KV_EINVAL for a
  * KV_POOL_DEVICE pool.  Every call on one GPU uses that GPU's one scratch array: calls that
  * overlap on one GPU (on two streams at once) race, and the caller must order them.

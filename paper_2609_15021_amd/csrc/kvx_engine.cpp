@@ -248,7 +248,7 @@ kv_status transfer(kv_pool *p, const kv_cache *cache, const int32_t *block_table
         int64_t copies = 0;
         for (int64_t i = 0; i < nc; ++i)
             copies += i % p->cpb == 0 || chunk_ids[i] != chunk_ids[i - 1] + 1;
-        direct = kvx::moves_directly(p, n_tokens * g.token_bytes, copies);
+        direct = kvx::moves_directly(p, dir, n_tokens * g.token_bytes, copies);
     }
     if (direct) {
         std::vector<int32_t> slots(static_cast<size_t>(nc));
@@ -363,7 +363,7 @@ kv_status transfer_state(kv_pool *p, const kv_state *st, const int64_t *pages, i
         int64_t copies = n * S / (static_cast<int64_t>(p->cpb) * p->geo.slot_bytes);
         for (int64_t k = 0; k < n; ++k)
             copies += k == 0 || slot_ids[k] != slot_ids[k - 1] + 1;
-        direct = kvx::moves_directly(p, n * S, copies);
+        direct = kvx::moves_directly(p, dir, n * S, copies);
     }
     if (direct) {
         const StatePlan plan(st, n, kvx::kStatePiece);
@@ -492,8 +492,10 @@ kv_status kv_pool_create(const kv_layout *layout, int64_t num_slots, const kv_po
         if (num_slots <= 0 || num_slots > INT32_MAX)
             return kvx::fail(KV_EINVAL, "num_slots must be in [1, 2^31-1] (got %lld)",
                              static_cast<long long>(num_slots));
-        if (opts->mode != KV_MODE_ZERO_COPY && opts->mode != KV_MODE_STAGED)
-            return kvx::fail(KV_EINVAL, "opts->mode must be KV_MODE_ZERO_COPY or KV_MODE_STAGED (got %u)", opts->mode);
+        if (opts->mode != KV_MODE_ZERO_COPY && !kvx::is_staged(opts->mode))
+            return kvx::fail(KV_EINVAL,
+                             "opts->mode must be KV_MODE_ZERO_COPY, KV_MODE_STAGED or KV_MODE_STAGED_DMA (got %u)",
+                             opts->mode);
         if (opts->host_kind != KV_HOST_COHERENT && opts->host_kind != KV_HOST_NONCOHERENT &&
             opts->host_kind != KV_POOL_DEVICE)
             return kvx::fail(KV_EINVAL, "unknown host_kind %u", opts->host_kind);
@@ -504,7 +506,7 @@ kv_status kv_pool_create(const kv_layout *layout, int64_t num_slots, const kv_po
         if (opts->chunks_per_batch < 0 || opts->chunks_per_batch > kvx::kMaxLaunchChunks)
             return kvx::fail(KV_EINVAL, "chunks_per_batch must be in [1, %d] (got %d)", kvx::kMaxLaunchChunks,
                              opts->chunks_per_batch);
-        const bool staged = opts->mode == KV_MODE_STAGED;
+        const bool staged = kvx::is_staged(opts->mode);
         const int cpb = (staged && opts->chunks_per_batch) ? opts->chunks_per_batch : kDefaultChunksPerBatch;
         // Zero-copy launches into host memory default to the largest launch (they stride a capped grid);
         // device-pool launches default to up to kDeviceLaunchBytes.
@@ -514,7 +516,7 @@ kv_status kv_pool_create(const kv_layout *layout, int64_t num_slots, const kv_po
         else if (on_device)  // check_layout has bounded the chunk: its bytes are positive
             zc_chunks = static_cast<int>(std::clamp<int64_t>(kDeviceLaunchBytes / kvx::geometry(*layout, 0).slot_bytes,
                                                              kDefaultChunksPerBatch, kvx::kMaxLaunchChunks));
-        const bool want_staging = opts->mode == KV_MODE_STAGED || opts->staging_slots > 0;
+        const bool want_staging = staged || opts->staging_slots > 0;
         const int K = opts->staging_slots ? opts->staging_slots : kDefaultStagingSlots;
         if (want_staging && (K < 2 || K > 64))
             return kvx::fail(KV_EINVAL, "staging_slots must be in [2, 64] (got %d)", K);
@@ -555,7 +557,7 @@ kv_status kv_pool_create(const kv_layout *layout, int64_t num_slots, const kv_po
             p->host_kind = opts->host_kind;
             p->profile = opts->profile != 0;
             p->zc_chunks = zc_chunks;
-            p->dma_only = staged && opts->chunks_per_batch != 0;
+            p->dma_only = opts->chunks_per_batch != 0;
 
             // On failure: free what was made, keeping the original error text.
             auto bail = [&](kv_status code) {
@@ -703,6 +705,7 @@ kv_status kv_pool_get_info(const kv_pool *pool, kv_pool_info *info) {
         info->device = pool->device;
         info->mode = pool->mode_of[kvx::kPack];
         info->load_mode = pool->mode_of[kvx::kUnpack];
+        info->direct_bytes = pool->dma_only ? 0u : static_cast<uint32_t>(kvx::kDirectBytes);
         info->host_kind = pool->host_kind;
         info->is_pinned = pool->pinned ? 1 : 0;
         info->staging_slots = pool->K;
@@ -741,9 +744,9 @@ kv_status kv_pool_set_modes(kv_pool *pool, uint32_t store_mode, uint32_t load_mo
             return kvx::fail(KV_EINVAL, "pool must not be NULL");
         std::lock_guard<std::mutex> lock(pool->mu);
         for (uint32_t mode : {store_mode, load_mode}) {
-            if (mode != KV_MODE_ZERO_COPY && mode != KV_MODE_STAGED)
+            if (mode != KV_MODE_ZERO_COPY && !kvx::is_staged(mode))
                 return kvx::fail(KV_EINVAL, "unknown mode %u", mode);
-            if (mode == KV_MODE_STAGED && !pool->staging)
+            if (kvx::is_staged(mode) && !pool->staging)
                 return kvx::fail(KV_EINVAL, "pool was created without staging; staged mode unavailable");
         }
         pool->mode_of[kvx::kPack] = store_mode;

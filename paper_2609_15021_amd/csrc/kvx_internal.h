@@ -200,7 +200,7 @@ struct kv_pool {
     bool staging_contiguous = false;  // always false: staging is plain device memory
     Lane lane[2];                    // [kPack] stores, [kUnpack] loads
     int zc_chunks = 0;                 // chunks per zero-copy launch
-    bool dma_only = false;             // chunks_per_batch was given: no staged request moves directly
+    bool dma_only = false;             // chunks_per_batch was given: as KV_MODE_STAGED_DMA in either direction
     // Last use of the pool on each caller stream (recorded after every store/load), so that
     // kv_pool_destroy never frees memory that queued kernels or copies still touch.
     std::vector<std::pair<hipStream_t, hipEvent_t>> last_use;
@@ -231,6 +231,8 @@ struct kv_pool {
 };
 
 namespace kvx {
+inline bool is_staged(uint32_t mode) { return mode == KV_MODE_STAGED || mode == KV_MODE_STAGED_DMA; }
+
 // Whether a staged request of `bytes` in `copies` DMA copies moves directly instead: by the zero-copy
 // kernels on the caller's stream.  Two kinds of request are better off so.
 //  * Short ones: the staged pipeline's kernel, event, cross-queue wait and copy cost about 65 us before and
@@ -242,8 +244,10 @@ namespace kvx {
 //    4 MiB: 50 of 57), so below 2 MiB a copy the link is idle for a quarter of the time or more.
 constexpr int64_t kDirectBytes = int64_t{32} << 20;
 constexpr int64_t kDirectCopyBytes = int64_t{2} << 20;
-inline bool moves_directly(const kv_pool *pool, int64_t bytes, int64_t copies) {
-    return !pool->dma_only && (bytes <= kDirectBytes || bytes / copies < kDirectCopyBytes);
+inline bool moves_directly(const kv_pool *pool, Direction dir, int64_t bytes, int64_t copies) {
+    if (pool->dma_only || pool->mode_of[dir] == KV_MODE_STAGED_DMA)
+        return false;
+    return bytes <= kDirectBytes || bytes / copies < kDirectCopyBytes;
 }
 
 // Make the pool's tier stream and block-table buffers (at least `table_bytes` each) if they are

@@ -89,7 +89,7 @@ kv_status kv_load_noalloc(const kv_cache *cache, const int32_t *block_table, int
         const int64_t fit = std::min<int64_t>(kScratchBytes / g.slot_bytes, kvx::kMaxLaunchChunks);
         for (int64_t i = 0; i < nc; ++i)
             copies += i % fit == 0 || chunk_ids[i] != chunk_ids[i - 1] + 1;
-        if (kvx::moves_directly(pool, n_tokens * g.token_bytes, copies)) {
+        if (kvx::moves_directly(pool, kvx::kUnpack, n_tokens * g.token_bytes, copies)) {
             int32_t slots[kvx::kMaxLaunchChunks];
             for (int64_t c0 = 0; c0 < nc; c0 += kvx::kMaxLaunchChunks) {
                 const int n = static_cast<int>(std::min<int64_t>(kvx::kMaxLaunchChunks, nc - c0));

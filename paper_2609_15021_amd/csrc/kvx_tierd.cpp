@@ -107,6 +107,8 @@ int usage(const char *msg) {
 bool parse_mode(const std::string &s, uint32_t *mode) {
     if (s == "staged")
         *mode = KV_MODE_STAGED;
+    else if (s == "staged_dma")
+        *mode = KV_MODE_STAGED_DMA;
     else if (s == "zero_copy")
         *mode = KV_MODE_ZERO_COPY;
     else
@@ -158,7 +160,7 @@ int main(int argc, char **argv) {
     const size_t plus = mode_s.find('+');
     if (!parse_mode(mode_s.substr(0, plus), &store_mode) ||
         !parse_mode(plus == std::string::npos ? mode_s : mode_s.substr(plus + 1), &load_mode))
-        return usage("--mode must be staged, zero_copy or STORE+LOAD of those");
+        return usage("--mode must be staged, staged_dma, zero_copy or STORE+LOAD of those");
     if (index_slots < 0)
         index_slots = slots;
 
@@ -170,7 +172,7 @@ int main(int argc, char **argv) {
     kv_pool_options opts;
     std::memset(&opts, 0, sizeof(opts));
     opts.mode = store_mode;
-    opts.staging_slots = (store_mode == KV_MODE_STAGED || load_mode == KV_MODE_STAGED) ? staging_slots : 0;
+    opts.staging_slots = (store_mode != KV_MODE_ZERO_COPY || load_mode != KV_MODE_ZERO_COPY) ? staging_slots : 0;
     opts.chunks_per_batch = cpb;
     opts.num_state_slots = state_slots;
     opts.state_slot_bytes = state_bytes;

@@ -29,6 +29,7 @@ KV_EBUSY = -6
 
 KV_MODE_ZERO_COPY = 1
 KV_MODE_STAGED = 2
+KV_MODE_STAGED_DMA = 3
 KV_HOST_COHERENT = 0
 KV_HOST_NONCOHERENT = 1
 KV_POOL_DEVICE = 2
@@ -38,7 +39,7 @@ KV_BLOCK_NHD = 1
 KV_LOOKUP_REQUIRE_STATE = 1
 KV_LOOKUP_PIN = 2
 
-MODES = {"zero_copy": KV_MODE_ZERO_COPY, "staged": KV_MODE_STAGED}
+MODES = {"zero_copy": KV_MODE_ZERO_COPY, "staged": KV_MODE_STAGED, "staged_dma": KV_MODE_STAGED_DMA}
 
 
 class KvLayout(ctypes.Structure):
@@ -70,7 +71,7 @@ class KvPoolInfo(ctypes.Structure):
                 ("staging_contiguous", ctypes.c_int32), ("host_base", ctypes.c_void_p),
                 ("device_base", ctypes.c_void_p), ("num_state_slots", ctypes.c_int64),
                 ("state_slot_bytes", ctypes.c_int64), ("state_host_base", ctypes.c_void_p),
-                ("load_mode", ctypes.c_uint32), ("pad", ctypes.c_uint32)]
+                ("load_mode", ctypes.c_uint32), ("direct_bytes", ctypes.c_uint32)]
 
 
 class KvState(ctypes.Structure):
