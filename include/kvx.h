@@ -90,10 +90,11 @@ typedef int32_t kv_status;
 /* Host transfer modes (chosen explicitly and reported in kv_pool_info, cf. Sec. 3.2). */
 #define KV_MODE_ZERO_COPY 1u  /* gather/scatter kernels on `stream` access mapped pinned memory directly */
 #define KV_MODE_STAGED 2u     /* pack/unpack in device staging on `stream`; DMA copies on event-gated side streams.
-                                 Part of the mode: requests of at most 32 MiB, or whose copies would average under
-                                 2 MiB, move by the zero-copy kernels instead.  Result and ordering are the same
-                                 and the request is faster on an idle GPU, but it takes CUs from other streams'
-                                 work meanwhile, as zero-copy mode does */
+                                 Part of the mode: requests of at most 32 MiB, and those of at most 256 MiB whose
+                                 copies would average under 2 MiB, move by the zero-copy kernels instead.  Result
+                                 and ordering are the same and the request is faster on an idle GPU, but it takes
+                                 CUs from other streams' work meanwhile, as zero-copy mode does (beside large
+                                 GEMMs it costs half of their rate while it runs, a staged one 1-8%) */
 #define KV_MODE_STAGED_DMA 3u /* staged, with every request on the DMA engines, short and fragmented ones too */
 
 /* Pool memory kinds. */

@@ -235,19 +235,24 @@ inline bool is_staged(uint32_t mode) { return mode == KV_MODE_STAGED || mode == 
 
 // Whether a staged request of `bytes` in `copies` DMA copies moves directly instead: by the zero-copy
 // kernels on the caller's stream.  Two kinds of request are better off so.
-//  * Short ones: the staged pipeline's kernel, event, cross-queue wait and copy cost about 65 us before and
-//    after the link's own time, a zero-copy kernel about 20 (store of 16 KiB: 85 us staged, 24 direct; 1 MiB:
-//    92 and 41; 16 MiB: 444 and 320; 32 MiB: 675 and 605; 128 MiB: 2,500 and 2,376).  Beyond 32 MiB (0.6 ms)
-//    the gain is under 10% and the kernels' hold on CUs lasts: a stream of large GEMMs beside a long
-//    zero-copy restore loses 30%, beside a staged one 0.5%.
+//  * Short ones: the staged pipeline's kernel, event, cross-queue wait and copy cost 50 to 75 us beyond the
+//    link's time, a zero-copy kernel about 20 (16 KiB stored in 85 us staged, 24 direct; 1 MiB in 92 and 41;
+//    16 MiB in 444 and 320; 32 MiB in 675 and 605).  At 32 MiB (0.6 ms) the gain is down to a tenth.
 //  * Fragmented ones: a copy costs the DMA engine about 10 us however short (256 KiB: 18 GB/s, 1 MiB: 37,
-//    4 MiB: 50 of 57), so below 2 MiB a copy the link is idle for a quarter of the time or more.
+//    4 MiB: 50 of 57), a fifth of the time at 2 MiB a copy.  256 MiB loaded in copies of 256 KiB, 1 MiB and
+//    1.5 MiB: 17.4, 7.6 and 6.7 ms staged, 4.7 direct.
+// The kernels hold CUs meanwhile: a stream of large GEMMs ran at 53-58% of its rate beside these loads and
+// at 43-53% beside these stores, at 92-99% beside staged ones, and a request that finds the GPU full waits for
+// a kernel to end by either route (16 and 32 MiB beside those GEMMs: 870 and 990 us direct, 800 and 810
+// staged).  So both kinds are bounded, to about 0.6 and 5 ms of the link's time, and longer requests stay on the
+// DMA engines.
 constexpr int64_t kDirectBytes = int64_t{32} << 20;
+constexpr int64_t kDirectFragmentedBytes = int64_t{256} << 20;
 constexpr int64_t kDirectCopyBytes = int64_t{2} << 20;
 inline bool moves_directly(const kv_pool *pool, Direction dir, int64_t bytes, int64_t copies) {
     if (pool->dma_only || pool->mode_of[dir] == KV_MODE_STAGED_DMA)
         return false;
-    return bytes <= kDirectBytes || bytes / copies < kDirectCopyBytes;
+    return bytes <= kDirectBytes || (bytes <= kDirectFragmentedBytes && bytes / copies < kDirectCopyBytes);
 }
 
 // Make the pool's tier stream and block-table buffers (at least `table_bytes` each) if they are

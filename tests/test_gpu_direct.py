@@ -1,5 +1,5 @@
 """GPU parity of staged requests at the edges of the rule that moves short and fragmented ones directly
-(at most 32 MiB, or copies averaging under 2 MiB), bit-exact against the CPU oracle, with the route each
+(at most 32 MiB, or 256 MiB in copies averaging under 2 MiB), bit-exact against the CPU oracle, with the route each
 took read off its launch count (for the no-allocation restore, off the copies in a captured graph); direct and
 staged requests ordered against each other on one stream; and the no-allocation restore by either route, also
 captured into a graph.
@@ -193,6 +193,33 @@ def test_requests_kept_on_the_dma_engines(how, launches, copies, direct_bytes):
     s.synchronize()
     assert np.array_equal(to_host(dB, A), want_B)
     assert _copies_in_graph(lambda: kvx.kv_load_noalloc(cB, tB, n, pool, ids, s), s) == copies
+    kvx.kv_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("n,direct", [(8 * EDGE, True), (8 * EDGE + 1, False)])
+def test_long_fragmented_requests_stay_on_the_dma_engines(n, direct):
+    """Scattered 256 KiB chunks, 256 MiB and one token more: what is stored comes back, by launches of 256 chunks
+    over the link or of 16 in staging."""
+    nc, nblk = TINY.nc(n), TINY.nblk(n)
+    ids = np.arange(2 * nc - 2, -1, -2)
+    pool = kvx.kv_pool_create(TINY.kv, 2 * nc, "staged", profile=True)
+    src = torch.randint(-(1 << 15), 1 << 15, (2, nblk, 2, 2, 16, 64), dtype=torch.int16, device=DEV)
+    dst = torch.zeros_like(src)
+    tA = bt_tensor(harness.block_table(11, nblk, nblk))
+    tB = bt_tensor(harness.block_table(12, nblk, nblk))
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    kvx.kv_store(kvx.Cache(src, TINY.kv, nblk), tA, n, pool, ids, s)
+    kvx.kv_load(kvx.Cache(dst, TINY.kv, nblk), tB, n, pool, ids, s)
+    want = -(-nc // (256 if direct else 16))
+    assert _launches(pool) == [want, want]
+    got, stored = dst[:, tB.long()], src[:, tA.long()]
+    used = n - (nblk - 1) * 16  # tokens in the last block
+    stored[:, -1, :, :, used:] = 0
+    assert torch.equal(got, stored)
+    c = kvx.Cache(dst, TINY.kv, nblk)
+    copies = _copies_in_graph(lambda: kvx.kv_load_noalloc(c, tB, n, pool, ids, s), s)
+    assert copies == (0 if direct else nc)
     kvx.kv_pool_destroy(pool)
 
 
