@@ -68,16 +68,18 @@ def test_direct_rule_edges(n, run, batch, direct):
     kvx.kv_pool_destroy(pool)
 
 
-def test_direct_and_staged_requests_are_ordered_on_one_stream():
+@pytest.mark.parametrize("kind", [kvx.KV_HOST_COHERENT, kvx.KV_HOST_NONCOHERENT])
+def test_direct_and_staged_requests_are_ordered_on_one_stream(kind):
     """No host wait in between: direct stores of quarters, a staged load of all of them, a staged store of
-    another cache over the same slots, then a direct load of a quarter."""
+    another cache over the same slots, then a direct load of a quarter.  Kernels and copy engines take turns on the
+    same bytes, in coherent memory and in memory that the GPU may cache."""
     n, nc = EDGE + 4096, TINY.nc(EDGE + 4096)
     ids = np.arange(nc)
     seed = harness.sub_seed("direct", "mixed")
     nb = TINY.nblk(n) + 32
     A, A2 = host_cache(TINY, nb, seed, "raw"), host_cache(TINY, nb, seed + 9, "raw")
     bt = harness.block_table(seed + 1, nb, TINY.nblk(n))
-    pool = kvx.kv_pool_create(TINY.kv, nc, "staged")
+    pool = kvx.kv_pool_create(TINY.kv, nc, "staged", host_kind=kind)
     dA, dA2 = to_device(A), to_device(A2)
     t = bt_tensor(bt)
     q = nc // 4 * 256
@@ -86,6 +88,7 @@ def test_direct_and_staged_requests_are_ordered_on_one_stream():
         B, B2 = device_cache(TINY, nb, fill=0), device_cache(TINY, nb, fill=0)
         kvx.pool_view(pool)[:] = 0
         torch.cuda.synchronize()
+        dA, dA2 = dA2, dA  # no byte keeps its value from one repeat to the next
         for k in range(4):
             kvx.kv_store(kvx.Cache(dA, TINY.kv, nb), t[k * q // 16:], q, pool, ids[k * q // 256:], s)
         kvx.kv_load(kvx.Cache(B, TINY.kv, nb), t, n, pool, ids, s)
