@@ -5,6 +5,8 @@ Expected values always come from the oracle applied to host-generated inputs
 """
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -88,3 +90,26 @@ def first_mismatch(got: np.ndarray, want: np.ndarray) -> str:
     if bad.size == 0:
         return "equal"
     return f"{bad.size} bytes differ; first at byte {bad[0]}: got {g[bad[0]]} want {w[bad[0]]}"
+
+
+def copies_in_graph(call, stream):
+    """Copy nodes in a graph that captured `call` (kv_load_noalloc: one per DMA copy, none on the direct route)."""
+    hip = ctypes.CDLL("libamdhip64.so.7")  # the runtime that torch has loaded
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t()
+    handle = ctypes.c_void_p(stream.cuda_stream)
+    assert hip.hipStreamBeginCapture(handle, 2) == 0  # relaxed
+    try:
+        call()
+    finally:
+        assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    kinds = []
+    for node in nodes:
+        kind = ctypes.c_int()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        kinds.append(kind.value)
+    assert hip.hipGraphDestroy(graph) == 0
+    assert set(kinds) <= {0, 1}, kinds  # kernels and copies
+    return kinds.count(1)

@@ -18,6 +18,8 @@ pytestmark = pytest.mark.gpu
 
 POOL_SENT = 0xA5
 CACHE_SENT = 0x5A
+# Requests of these sizes move by the zero-copy kernels in a "staged" pool too; "staged_dma" is the staging ring.
+MODES = ["zero_copy", "staged", "staged_dma"]
 
 
 def _round_trip(lay: Layout, NB: int, n: int, mode: str, host_kind=0, shuffled=False, dist="u11", seed_tag="t",
@@ -55,7 +57,7 @@ def _round_trip(lay: Layout, NB: int, n: int, mode: str, host_kind=0, shuffled=F
     kvx.kv_pool_destroy(pool)
 
 
-@pytest.mark.parametrize("mode", ["zero_copy", "staged"])
+@pytest.mark.parametrize("mode", MODES)
 @pytest.mark.parametrize("host_kind", [kvx.KV_HOST_COHERENT, kvx.KV_HOST_NONCOHERENT])
 @pytest.mark.parametrize("shuffled", [False, True])
 def test_tiny_config_round_trip(mode, host_kind, shuffled):
@@ -64,7 +66,7 @@ def test_tiny_config_round_trip(mode, host_kind, shuffled):
     _round_trip(TINY, 512, 4096, mode, host_kind, shuffled)
 
 
-@pytest.mark.parametrize("mode", ["zero_copy", "staged"])
+@pytest.mark.parametrize("mode", MODES)
 @pytest.mark.parametrize("n", [4096 + 192, 4096 + 128, 4096 + 64, 4096 + 1, 4, 17, 1, 255, 257])
 def test_partial_chunks_and_blocks(mode, n):
     """Partial final chunk (compact r*TB bytes, slot tail untouched) and partial final block."""
@@ -88,7 +90,7 @@ def test_layout_variants(mode, dims):
     _round_trip(lay, NB, n, mode, shuffled=True, dist="raw", staging_slots=2, chunks_per_batch=2)
 
 
-@pytest.mark.parametrize("mode", ["zero_copy", "staged"])
+@pytest.mark.parametrize("mode", MODES)
 def test_all_16bit_patterns_bit_exact(mode):
     """Raw bit patterns (NaN payloads, +-Inf, -0, subnormals as bf16) survive the GPU path."""
     _round_trip(TINY, 512, 4096, mode, dist="raw", seed_tag="raw")
@@ -101,7 +103,7 @@ def test_small_staging_ring_many_batches(mode):
                 side_streams=2)
 
 
-@pytest.mark.parametrize("mode", ["zero_copy", "staged"])
+@pytest.mark.parametrize("mode", MODES)
 def test_padded_block_stride(mode):
     """Blocks with padding between them: padding is neither read into chunks nor written."""
     lay = TINY
@@ -137,7 +139,7 @@ def test_padded_block_stride(mode):
     kvx.kv_pool_destroy(pool)
 
 
-@pytest.mark.parametrize("mode", ["zero_copy", "staged"])
+@pytest.mark.parametrize("mode", MODES)
 def test_load_into_disjoint_blocks_of_same_allocation(mode):
     """Tiny config: 256 source blocks and 256 disjoint destination blocks in one 512-block
     allocation; the load never touches the source blocks."""
@@ -211,10 +213,11 @@ def test_zero_tokens_is_noop(mode):
     kvx.kv_pool_destroy(pool)
 
 
-@pytest.mark.parametrize("mode", ["zero_copy", "staged"])
+@pytest.mark.parametrize("mode", MODES)
 def test_out_of_range_block_is_flagged_and_skipped(mode):
     """A block id outside [0, num_blocks) is reported, its cache block is never read, and its
-    chunk rows are zeros in both modes (no stale staging bytes reach the shared pool)."""
+    chunk rows are zeros in every mode (no stale staging bytes reach the shared pool): the pool and
+    every staging slot hold another request's bytes first."""
     lay, NB, n = TINY, 64, 512
     seed = harness.sub_seed("badblock")
     A = host_cache(lay, NB, seed, "u11")
@@ -224,9 +227,14 @@ def test_out_of_range_block_is_flagged_and_skipped(mode):
     bad[20] = -3
     pool = kvx.kv_pool_create(lay.kv, 2, mode)
     view = kvx.pool_view(pool)
-    view[:] = POOL_SENT
     dA = to_device(A)
     c = kvx.Cache(dA, lay.kv, NB)
+    ones = torch.full_like(dA, -1)
+    for _ in range(3):  # the ring's three slots
+        kvx.kv_store(kvx.Cache(ones, lay.kv, NB), bt_tensor(bt), n, pool, [0, 1])
+    torch.cuda.synchronize()
+    assert np.all(view == 0xFF) and kvx.kv_pool_async_error(pool) == 0
+    view[:] = POOL_SENT
     t = bt_tensor(bad)
     kvx.kv_store(c, t, n, pool, [0, 1])
     torch.cuda.synchronize()

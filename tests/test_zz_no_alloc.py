@@ -12,7 +12,7 @@ import harness
 import oracle
 from harness import gpu as hg
 from paper_2609_15021_amd import kvx
-from tests.gpu_support import (B27, DEV, TINY, bt_tensor, first_mismatch, host_cache, oracle_pool,
+from tests.gpu_support import (B27, DEV, TINY, bt_tensor, copies_in_graph, first_mismatch, host_cache, oracle_pool,
                                oracle_unpack_into, to_device, to_host)
 
 pytestmark = pytest.mark.gpu
@@ -34,10 +34,11 @@ def _noalloc(cache, block_table, n, pool, chunk_ids, stream):
         raise kvx.KvError(st, kvx.kv_last_error())
 
 
-@pytest.mark.parametrize("mode", ["staged", "zero_copy"])
+@pytest.mark.parametrize("mode", ["staged", "zero_copy", "staged_dma"])
 def test_noalloc_matches_kv_load_tiny(mode):
     """Tiny layout: a 17-chunk restore with a partial chunk and shuffled slots, then a smaller
-    4-chunk restore into other blocks; both equal kv_load's result and the oracle's."""
+    4-chunk restore into other blocks; both equal kv_load's result and the oracle's.  Requests of
+    this size go through the scratch in "staged_dma" only, as a captured call's copies show."""
     lay, NB = TINY, 512
     seed = harness.sub_seed("noalloc", "tiny")
     A = host_cache(lay, NB, seed, "raw")
@@ -71,6 +72,9 @@ def test_noalloc_matches_kv_load_tiny(mode):
         want = oracle_unpack_into(lay, B0, btB, n, want_pool[:], ids)
         g = to_host(got, A)
         assert np.array_equal(g, want), f"call {call}: " + first_mismatch(g, want)
+        cache = kvx.Cache(got, lay.kv, NB)
+        copies = copies_in_graph(lambda: _noalloc(cache, tB, n, pool, ids, s), s)
+        assert (copies > 0) == (mode == "staged_dma"), copies
     assert kvx.kv_pool_async_error(pool) == 0
     kvx.kv_pool_destroy(pool)
 
@@ -105,17 +109,18 @@ def test_noalloc_matches_kv_load_27b():
     kvx.kv_pool_destroy(pool)
 
 
+@pytest.mark.parametrize("route", ["direct", "scratch"])
 @pytest.mark.parametrize("i", range(24))
-def test_noalloc_random_layouts(i):
+def test_noalloc_random_layouts(i, route):
     """Seeded random layouts (the random-layout parity cases' generator: 1-5 layers, 1-8 heads,
     16-128-byte rows of 1-, 2- and 4-byte elements, 1-32-token blocks, packed and padded strides,
     both block orders, partial chunks, shuffled ids), the pool filled with the CPU oracle's packed
     bytes: a restore of the whole prefix, then a shorter one into another cache; each equals the
-    oracle's cache bytes, sentinels included."""
+    oracle's cache bytes, sentinels included.  By the zero-copy kernels, and through the scratch."""
     from tests.test_gpu_fuzz import ORDERS, _case
     lay, n, NB, stride, order, num_slots, _ = _case(i)
     mode = ("staged", "zero_copy")[i % 2]
-    print(f"[noalloc] case {i} {mode}: L{lay.L} H{lay.H} D{lay.D} E{lay.E} BS{lay.BS} C{lay.C} n={n} NB={NB} "
+    print(f"[noalloc] case {i} {mode} {route}: L{lay.L} H{lay.H} D{lay.D} E{lay.E} BS{lay.BS} C{lay.C} n={n} NB={NB} "
           f"stride={stride} order={order} slots={num_slots}", flush=True)
     seed = harness.sub_seed("noalloc-fuzz", i)
     rng = np.random.default_rng(seed)
@@ -124,7 +129,7 @@ def test_noalloc_random_layouts(i):
     ids = harness.chunk_ids(lay.nc(n), num_slots, seed + 3)
     want_pool = np.full(num_slots * lay.slot_bytes, 0xA5, dtype=np.uint8)
     assert oracle.pack(lay.orc, A, stride, NB, btA, n, want_pool, ids, 4, block_order=ORDERS[order]) == oracle.OK
-    pool = kvx.kv_pool_create(lay.kv, num_slots, mode)
+    pool = kvx.kv_pool_create(lay.kv, num_slots, mode, chunks_per_batch=2 if route == "scratch" else 0)
     kvx.pool_view(pool)[:] = want_pool
     s = torch.cuda.Stream()
     for call, m in enumerate((n, max(1, n // 3))):
@@ -134,11 +139,14 @@ def test_noalloc_random_layouts(i):
                              block_order=ORDERS[order]) == oracle.OK
         dB = [torch.full((NB * stride,), SENT, dtype=torch.uint8, device=DEV) for _ in range(lay.L)]
         torch.cuda.synchronize()
-        _noalloc(kvx.Cache(dB, lay.kv, NB, stride, order), bt_tensor(btB), m, pool, ids[:lay.nc(m)], s)
+        cache, tB = kvx.Cache(dB, lay.kv, NB, stride, order), bt_tensor(btB)
+        _noalloc(cache, tB, m, pool, ids[:lay.nc(m)], s)
         s.synchronize()
         for l in range(lay.L):
             got = dB[l].cpu().numpy()
             assert np.array_equal(got, want[l]), f"call {call} (n={m}) layer {l}: " + first_mismatch(got, want[l])
+        copies = copies_in_graph(lambda: _noalloc(cache, tB, m, pool, ids[:lay.nc(m)], s), s)
+        assert (copies > 0) == (route == "scratch"), copies
     assert kvx.kv_pool_async_error(pool) == 0
     kvx.kv_pool_destroy(pool)
 
@@ -163,17 +171,19 @@ def test_noalloc_refuses_what_it_cannot_do():
     kvx.kv_pool_destroy(dpool)
 
 
-def test_noalloc_replays_under_graph_capture():
+@pytest.mark.parametrize("mode", ["staged", "staged_dma"])
+def test_noalloc_replays_under_graph_capture(mode):
     """The callers this entry point is for include code under graph capture: the restore is captured
     into a HIP graph and replayed three times, with eager work and synchronisation between the
-    replays; every replay must leave exactly kv_load's result (checked after each replay)."""
+    replays; every replay must leave exactly kv_load's result (checked after each replay).  By the
+    zero-copy kernels, and through the scratch ("staged_dma")."""
     lay, NB = TINY, 512
     seed = harness.sub_seed("noalloc", "graph")
     A = host_cache(lay, NB, seed, "raw")
     n = 4096 + 192
     nc = lay.nc(n)
     cid = harness.chunk_ids(nc, nc + 2, seed + 3)
-    pool = kvx.kv_pool_create(lay.kv, nc + 2, "staged")
+    pool = kvx.kv_pool_create(lay.kv, nc + 2, mode)
     dA = to_device(A)
     s = torch.cuda.Stream()
     torch.cuda.synchronize()
