@@ -116,10 +116,9 @@ kv_status check_device(const kv_pool *p, int buffers_device) {
 
 // Enqueue the pack/unpack kernels for chunks [chunk0, chunk0 + nchunks) of the prefix.
 // slots[c] is the slot id of chunk chunk0 + c relative to chunk_base (slot_stride apart);
-// host_side: chunk_base is the mapped pinned pool (zero-copy) rather than device staging.
 kv_status enqueue_gather(kv_pool *p, const kv_cache *cache, const int32_t *block_table, int64_t n_tokens,
                          Direction dir, int64_t chunk0, int nchunks, const int32_t *slots, uint8_t *chunk_base,
-                         int64_t slot_stride, bool host_side, hipStream_t stream) {
+                         int64_t slot_stride, kvx::Packed packed, hipStream_t stream) {
     const Geometry &g0 = p->geo;
     hipEvent_t t_start = nullptr, t_stop = nullptr;
     if (p->profile) {
@@ -133,7 +132,7 @@ kv_status enqueue_gather(kv_pool *p, const kv_cache *cache, const int32_t *block
     }
     int64_t payload = 0;
     KVX_HIP(kvx::launch_gathers(cache, block_table, n_tokens, dir, chunk0, nchunks, slots, chunk_base, slot_stride,
-                                host_side, p->err_dev, stream));
+                                packed, p->err_dev, stream));
     for (int c = 0; c < nchunks; ++c) {
         const int64_t i = chunk0 + c;
         const int64_t r = std::min<int64_t>(g0.C, n_tokens - i * g0.C);
@@ -257,7 +256,7 @@ kv_status transfer(kv_pool *p, const kv_cache *cache, const int32_t *block_table
         for (int64_t c0 = 0; c0 < nc; c0 += p->zc_chunks) {
             const int n = static_cast<int>(std::min<int64_t>(p->zc_chunks, nc - c0));
             kv_status st = enqueue_gather(p, cache, block_table, n_tokens, dir, c0, n, slots.data() + c0,
-                                          p->dev_base, g.slot_bytes, !p->on_device, stream);
+                                          p->dev_base, g.slot_bytes, kvx::packed_in_pool(p), stream);
             if (st != KV_OK)
                 return st;
         }
@@ -282,7 +281,7 @@ kv_status transfer(kv_pool *p, const kv_cache *cache, const int32_t *block_table
         const int64_t c0 = b * p->cpb;
         const int n = static_cast<int>(std::min<int64_t>(p->cpb, nc - c0));
         return enqueue_gather(p, cache, block_table, n_tokens, dir, c0, n, local.data(), stage, g.slot_bytes,
-                              false, stream);
+                              kvx::kInDevice, stream);
     };
     return staged_pipeline(p, nbatches, runs_of, kernels, stream, dir);
 }

@@ -53,19 +53,22 @@ typedef uint32_t vec16 __attribute__((ext_vector_type(4)));
 #endif
 // Workgroups of a host-side (zero-copy) pack / unpack launch; each strides over the launch's tiles
 // with the next tile's reads in flight.  Measured on MI355X at the 27B-class layout: 64 for pack gives
-// 57.0 GB/s (48: 56.9, 32: 52.9).  Unpack is chosen by what a staged store running at the same time
-// leaves it: 16 gives 57.1 GB/s alone and 99.8 in total (15: 56.8 and 92.7, 17: 57.2 and 91.1, 18: 57.2
-// and 78.7, 32: 57.5 and 59.6); the earlier kernel took 32 workgroups for 57.0 and 97.2.  Where each lane
+// 57.0 GB/s (48: 56.9, 32: 52.9).  Alone, unpack moves 56.8 GB/s with 16, 57.1 with 20, 57.4 with 24 and 32.
+// With a store of the same pool running at the same time, the total follows from what the reads in flight leave
+// the store (store + load, GB/s, for 16 / 17 / 18 / 20 / 24 / 32 workgroups):
+//   store by DMA copies   98.5 / 85.6 / 75.2 / 66.8 / 60.0 / 59.4   (the same at 4 KiB slabs)
+//   store by kernels      69.4 / 71.5 / 72.9 / 75.5 / 78.7 / 86.6   (within 5% at 8 and 4 KiB slabs and token-major)
+// so loads take 16 in a pool whose stores run on the DMA engines and 32 where they are kernels.  Where each lane
 // has its own block (see start_tile) the wait for its table entry also waits for a tile's data, so it
-// takes twice as many for the same rate (160-byte rows: 16 move 47 GB/s, 32 move 56; before, 40).
+// takes 32 for the same rate (160-byte rows: 16 move 47 GB/s, 32 move 56).
 #ifndef KVX_HOST_WGS_PACK
 #define KVX_HOST_WGS_PACK 64
 #endif
 #ifndef KVX_HOST_WGS_UNPACK
-#define KVX_HOST_WGS_UNPACK 16
+#define KVX_HOST_WGS_UNPACK 32
 #endif
-#ifndef KVX_HOST_WGS_UNPACK_LANES
-#define KVX_HOST_WGS_UNPACK_LANES 32
+#ifndef KVX_HOST_WGS_UNPACK_BESIDE_DMA
+#define KVX_HOST_WGS_UNPACK_BESIDE_DMA 16
 #endif
 #ifndef KVX_TILE_VECS
 #define KVX_TILE_VECS 256
@@ -278,7 +281,8 @@ static const void *kernel_of(Direction dir, bool wave) {
 }
 
 // Launch over the chunks and layers that `a` names; what depends on the layout alone is set.
-static hipError_t launch(GatherArgs &a, Direction dir, bool host_side, hipStream_t stream) {
+static hipError_t launch(GatherArgs &a, Direction dir, Packed packed, hipStream_t stream) {
+    const bool host_side = packed != kInDevice;
     auto tiles_of = [&](int64_t r) { return (r * a.token_vecs + kTileVecs - 1) / kTileVecs; };
     a.last_tiles = static_cast<int32_t>(tiles_of(a.last_r));
     a.tiles = a.nchunks > 1 ? static_cast<int32_t>(tiles_of(a.C)) : a.last_tiles;
@@ -288,10 +292,10 @@ static hipError_t launch(GatherArgs &a, Direction dir, bool host_side, hipStream
     if (strided) {
         const int64_t total = 2 * static_cast<int64_t>(a.nlayers) *
                               ((a.nchunks - 1) * static_cast<int64_t>(a.tiles) + a.last_tiles);
-        const int64_t wgs = !host_side     ? kStridedDeviceWgs
-                            : dir == kPack ? KVX_HOST_WGS_PACK
-                            : wave         ? KVX_HOST_WGS_UNPACK
-                                           : KVX_HOST_WGS_UNPACK_LANES;
+        const int64_t wgs = !host_side                           ? kStridedDeviceWgs
+                            : dir == kPack                       ? KVX_HOST_WGS_PACK
+                            : wave && packed == kInHostBesideDma ? KVX_HOST_WGS_UNPACK_BESIDE_DMA
+                                                                 : KVX_HOST_WGS_UNPACK;
         grid = dim3(static_cast<uint32_t>(std::min(total, wgs)));
     }
     const void *fn = strided ? kernel_of<true>(dir, wave) : kernel_of<false>(dir, wave);
@@ -303,7 +307,7 @@ static hipError_t launch(GatherArgs &a, Direction dir, bool host_side, hipStream
 
 hipError_t launch_gathers(const kv_cache *cache, const int32_t *block_table, int64_t n_tokens, Direction dir,
                           int64_t chunk0, int nchunks, const int32_t *slots, uint8_t *chunk_base, int64_t slot_stride,
-                          bool host_side, int32_t *err, hipStream_t stream) {
+                          Packed packed, int32_t *err, hipStream_t stream) {
     const Geometry g = geometry(cache->layout, cache->block_stride_bytes);
     GatherArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -333,7 +337,7 @@ hipError_t launch_gathers(const kv_cache *cache, const int32_t *block_table, int
             a.last_r = static_cast<int32_t>(std::min<int64_t>(g.C, n_tokens - (chunk0 + c0 + a.nchunks - 1) * g.C));
             a.block_table = block_table + (chunk0 + c0) * g.blocks_per_chunk;
             std::copy(slots + c0, slots + c0 + a.nchunks, a.slot);
-            const hipError_t e = launch(a, dir, host_side, stream);
+            const hipError_t e = launch(a, dir, packed, stream);
             if (e != hipSuccess)
                 return e;
         }

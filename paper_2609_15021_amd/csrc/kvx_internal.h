@@ -95,6 +95,10 @@ struct GatherArgs {
 
 enum Direction { kPack = 0, kUnpack = 1 };
 
+// Where the packed side of a gather launch lies: device memory (staging, a device pool) or the mapped pinned pool,
+// in a pool whose stores are kernels too or whose stores run on the DMA engines.
+enum Packed { kInDevice = 0, kInHost = 1, kInHostBesideDma = 2 };
+
 // Kernel arguments of one state-snapshot launch.  Pages are cut into ppp pieces of `piece` <=
 // kStatePiece bytes (the last piece of a page may be shorter).  The launch covers npieces <=
 // kMaxLaunchPieces pieces of its own lists of snapshots, from piece piece0 of page page0 on; page
@@ -117,11 +121,11 @@ hipError_t launch_state(const StateArgs &args, Direction dir, bool host_side, hi
 
 // Enqueue the pack/unpack launches for chunks [chunk0, chunk0 + nchunks) of a prefix of `cache`
 // (split over launches of at most kMaxLaunchLayers layers and kMaxLaunchChunks chunks): slots[c] is the slot of chunk
-// chunk0 + c at chunk_base, slot_stride bytes apart; host_side: chunk_base is mapped pinned host
-// memory.  Returns the first launch error.  No host allocation, no event.
+// chunk0 + c at chunk_base, slot_stride bytes apart.  Returns the first launch error.  No host allocation, no
+// event.
 hipError_t launch_gathers(const kv_cache *cache, const int32_t *block_table, int64_t n_tokens, Direction dir,
                           int64_t chunk0, int nchunks, const int32_t *slots, uint8_t *chunk_base, int64_t slot_stride,
-                          bool host_side, int32_t *err, hipStream_t stream);
+                          Packed packed, int32_t *err, hipStream_t stream);
 
 // Thread-local error reporting.
 kv_status fail(kv_status code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
@@ -232,6 +236,11 @@ struct kv_pool {
 
 namespace kvx {
 inline bool is_staged(uint32_t mode) { return mode == KV_MODE_STAGED || mode == KV_MODE_STAGED_DMA; }
+
+// Where the kernels of a request that moves directly find the packed side.
+inline Packed packed_in_pool(const kv_pool *pool) {
+    return pool->on_device ? kInDevice : pool->mode_of[kPack] == KV_MODE_ZERO_COPY ? kInHost : kInHostBesideDma;
+}
 
 // Whether a staged request of `bytes` in `copies` DMA copies moves directly instead: by the zero-copy
 // kernels on the caller's stream.  Two kinds of request are better off so.

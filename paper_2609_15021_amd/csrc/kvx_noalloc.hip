@@ -96,7 +96,7 @@ kv_status kv_load_noalloc(const kv_cache *cache, const int32_t *block_table, int
                 for (int c = 0; c < n; ++c)
                     slots[c] = static_cast<int32_t>(chunk_ids[c0 + c]);
                 KVX_HIP(kvx::launch_gathers(cache, block_table, n_tokens, kvx::kUnpack, c0, n, slots, pool->dev_base,
-                                            g.slot_bytes, true, pool->err_dev, s));
+                                            g.slot_bytes, kvx::packed_in_pool(pool), pool->err_dev, s));
             }
             return KV_OK;
         }
@@ -129,7 +129,7 @@ kv_status kv_load_noalloc(const kv_cache *cache, const int32_t *block_table, int
                 run_bytes = bytes;
             }
             KVX_HIP(kvx::launch_gathers(cache, block_table, n_tokens, kvx::kUnpack, c0, nb, local, stage,
-                                        g.slot_bytes, false, pool->err_dev, s));
+                                        g.slot_bytes, kvx::kInDevice, pool->err_dev, s));
         }
         return KV_OK;
     });
