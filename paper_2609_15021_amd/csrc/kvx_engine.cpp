@@ -289,14 +289,27 @@ kv_status transfer(kv_pool *p, const kv_cache *cache, const int32_t *block_table
 // Piece arithmetic of one state request: n snapshots of G pages, each page cut into
 // ppp pieces of `piece` bytes (the last piece of a page may be shorter).  Piece q is
 // piece j of layer g of snapshot k with q = (k*G + g)*ppp + j; its packed bytes start
-// at off(q) in the concatenation of the n packed snapshots.
+// at off(q) in the concatenation of the n packed snapshots.  With `lines`, pages may be cut
+// up to a line earlier (StateArgs.lines), and off() holds at their starts only.
 struct StatePlan {
     int64_t n, G, page_bytes, page_stride, snap_bytes, piece, ppp, pieces;
+    bool lines = false;
 
-    StatePlan(const kv_state *st, int64_t n_snap, int64_t piece_bytes)
+    StatePlan(const kv_state *st, int64_t n_snap, int64_t piece_bytes, bool host_side)
         : n(n_snap), G(st->num_layers), page_bytes(st->page_bytes),
           page_stride(st->page_stride ? st->page_stride : st->page_bytes), snap_bytes(G * page_bytes),
-          piece(std::min(piece_bytes, page_bytes)), ppp((page_bytes + piece - 1) / piece), pieces(n * G * ppp) {}
+          piece(std::min(piece_bytes, page_bytes)), ppp((page_bytes + piece - 1) / piece) {
+        // Pages of a ragged length lie across lines of host memory, and a piece that starts inside a line costs a
+        // part of one more over the link.  48 pages of 3,693,968 bytes over the link (store / load, us): cut at the
+        // page's own offsets 3,170 / 3,198, at 64-byte addresses 3,136 / 3,163, 128 3,127 / 3,115, 256 3,109 /
+        // 3,089 (the earlier 16 KiB pieces 3,184 / 3,161).  Not where a short page would take one more piece.
+        const int64_t cut = (page_bytes + kvx::kHostLine - 16 + piece - 1) / piece;
+        if (host_side && page_bytes % kvx::kHostLine != 0 && (cut == ppp || ppp >= 16)) {
+            lines = true;
+            ppp = cut;
+        }
+        pieces = n * G * ppp;
+    }
 
     int64_t off(int64_t q) const {
         const int64_t per = G * ppp;
@@ -339,6 +352,7 @@ kv_status enqueue_state(kv_pool *p, const kv_state *st, const StatePlan &plan, c
         a.npieces = static_cast<int32_t>(q_end - q);
         a.G = static_cast<int32_t>(plan.G);
         a.ppp = static_cast<int32_t>(plan.ppp);
+        a.lines = plan.lines ? 1 : 0;
         for (int64_t k = k_first; k <= k_last; ++k) {
             a.page[k - k_first] = pages[k];
             a.off[k - k_first] = snap_off(k);
@@ -365,7 +379,7 @@ kv_status transfer_state(kv_pool *p, const kv_state *st, const int64_t *pages, i
         direct = kvx::moves_directly(p, dir, n * S, copies);
     }
     if (direct) {
-        const StatePlan plan(st, n, kvx::kStatePiece);
+        const StatePlan plan(st, n, kvx::kStatePiece, !p->on_device);
         auto off = [&](int64_t k) { return slot_ids[k] * S; };
         return enqueue_state(p, st, plan, pages, 0, plan.pieces, p->dev_base + p->state_offset, off, !p->on_device,
                              stream, dir);
@@ -373,7 +387,7 @@ kv_status transfer_state(kv_pool *p, const kv_state *st, const int64_t *pages, i
 
     // Staged mode: cut the pieces into batches of at most one staging slot of bytes.
     const int64_t cap = static_cast<int64_t>(p->cpb) * p->geo.slot_bytes;
-    const StatePlan plan(st, n, std::min<int64_t>(kvx::kStatePiece, cap / 16 * 16));
+    const StatePlan plan(st, n, std::min<int64_t>(kvx::kStatePiece, cap / 16 * 16), false);
     std::vector<int64_t> cut{0};
     while (cut.back() < plan.pieces) {
         const int64_t qa = cut.back(), oa = plan.off(qa);

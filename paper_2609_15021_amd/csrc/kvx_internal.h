@@ -23,6 +23,7 @@ constexpr int kMaxLaunchChunks = 256;  // slot ids carried in one launch's kerne
 constexpr int kMaxStateLayers = 64;    // recurrent layers of a state snapshot (one launch carries all)
 constexpr int kMaxLaunchSnapshots = 128;  // snapshots carried in one state launch's arguments
 constexpr int64_t kStatePiece = 4 * 1024;  // bytes of a page one workgroup moves (kvx_state.hip)
+constexpr int64_t kHostLine = 256;  // pieces of host memory start at multiples of this (see StatePlan)
 constexpr int64_t kMaxLaunchPieces = int64_t(1) << 22;  // workgroups of one state launch
 
 // Derived sizes of a layout (all bytes, 64-bit).
@@ -102,13 +103,15 @@ enum Packed { kInDevice = 0, kInHost = 1, kInHostBesideDma = 2 };
 // Kernel arguments of one state-snapshot launch.  Pages are cut into ppp pieces of `piece` <=
 // kStatePiece bytes (the last piece of a page may be shorter).  The launch covers npieces <=
 // kMaxLaunchPieces pieces of its own lists of snapshots, from piece piece0 of page page0 on; page
-// p is layer p % G of snapshot p / G.
+// p is layer p % G of snapshot p / G.  In a host-side launch with `lines` set, a page is cut at multiples of
+// kHostLine of its packed bytes' addresses: its first piece is shorter by the address's low bits.
 struct StateArgs {
     uint8_t *base;                     // device-visible packed side (state pool or staging)
     int64_t page_stride, page_bytes;
     int32_t page0, piece0, npieces, piece;
     int32_t G, ppp;
-    int32_t last_piece, pad;           // bytes of a page's last piece (set by launch_state, as the next)
+    int32_t last_piece;                // bytes of a page's last piece (set by launch_state, as the next)
+    int32_t lines;
     Divisor by_ppp, by_layers;         // division by ppp and G
     uint8_t *layer[kMaxStateLayers];   // device base of each recurrent layer's page buffer
     int64_t page[kMaxLaunchSnapshots];  // device page id of each snapshot

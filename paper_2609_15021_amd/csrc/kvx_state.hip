@@ -41,26 +41,38 @@ constexpr int kNt = 2, kSc1 = 16, kRawBuffer = 0x00020000;
 struct Piece {
     uint8_t *dst;
     int bytes;
+    int skip;  // bytes of lanes before the piece's first
     svec16 data;
 };
 
 // Start piece q of the launch (pieces run [snapshot k][layer g][piece of the page]): issue its reads.  The
 // buffer's range ends with the piece, so lanes beyond a short piece's end read zeros and write nothing: no
 // branch, no lane address, and so nothing that waits for an earlier piece's reads.
-template <int DIR>
+template <int DIR, bool LINES>
 __device__ __forceinline__ void start_piece(const StateArgs &a, int q, Piece &p) {
     const int t = a.piece0 + q, pages = divide(t, a.by_ppp);
     const int page_id = a.page0 + pages;  // k*G + g
     const int k = divide(page_id, a.by_layers), g = page_id - k * a.G;
     const int j = t - pages * a.ppp;
-    const int64_t start = static_cast<int64_t>(j) * a.piece;
-    p.bytes = j == a.ppp - 1 ? a.last_piece : a.piece;
-    uint8_t *page = a.layer[g] + a.page[k] * a.page_stride + start;
-    uint8_t *packed = a.base + a.off[k] + static_cast<int64_t>(g) * a.page_bytes + start;
+    int64_t start = static_cast<int64_t>(j) * a.piece;
+    uint8_t *page = a.layer[g] + a.page[k] * a.page_stride;
+    uint8_t *packed = a.base + a.off[k] + static_cast<int64_t>(g) * a.page_bytes;
+    if constexpr (LINES) {
+        const int64_t low = start - (static_cast<int>(reinterpret_cast<uintptr_t>(packed)) & (kHostLine - 1));
+        start = max(low, int64_t{0});
+        p.skip = static_cast<int>(start - low);
+        p.bytes = static_cast<int>(max(min(low + a.piece, a.page_bytes) - start, int64_t{0}));
+    } else {
+        p.skip = 0;
+        p.bytes = j == a.ppp - 1 ? a.last_piece : a.piece;
+    }
+    page += start;
+    packed += start;
     p.dst = DIR == kPack ? packed : page;
     const __amdgpu_buffer_rsrc_t src =
         __builtin_amdgcn_make_buffer_rsrc(DIR == kPack ? page : packed, 0, p.bytes, kRawBuffer);
-    p.data = __builtin_amdgcn_raw_buffer_load_b128(src, static_cast<int>(threadIdx.x) * 16, 0, kNt);
+    // (A lane before the piece has a negative offset, which the range check takes for one far beyond it.)
+    p.data = __builtin_amdgcn_raw_buffer_load_b128(src, static_cast<int>(threadIdx.x) * 16 - p.skip, 0, kNt);
 }
 
 // Write a started piece to its place; "nt sc1" where the gather kernels' stores take it (into the mapped
@@ -68,36 +80,37 @@ __device__ __forceinline__ void start_piece(const StateArgs &a, int q, Piece &p)
 template <int DIR, bool HOST_SIDE>
 __device__ __forceinline__ void finish_piece(const Piece &p) {
     const __amdgpu_buffer_rsrc_t dst = __builtin_amdgcn_make_buffer_rsrc(p.dst, 0, p.bytes, kRawBuffer);
-    __builtin_amdgcn_raw_buffer_store_b128(p.data, dst, static_cast<int>(threadIdx.x) * 16, 0,
+    __builtin_amdgcn_raw_buffer_store_b128(p.data, dst, static_cast<int>(threadIdx.x) * 16 - p.skip, 0,
                                            DIR == kUnpack || HOST_SIDE ? kNt | kSc1 : kNt);
 }
 
-template <int DIR, bool HOST_SIDE>
+// LINES: a host-side launch whose pages are cut at the lines of their packed bytes.
+template <int DIR, bool HOST_SIDE, bool LINES = false>
 __global__ __launch_bounds__(kThreads) void state_kernel(const StateArgs a) {
     if constexpr (!HOST_SIDE) {
         Piece p;
-        start_piece<DIR>(a, blockIdx.x, p);
+        start_piece<DIR, LINES>(a, blockIdx.x, p);
         finish_piece<DIR, HOST_SIDE>(p);
     } else {
         // Two pieces in turn, by name: copying one to the other would wait for its reads.
         const int end = a.npieces, step = static_cast<int>(gridDim.x);
         int q = static_cast<int>(blockIdx.x);  // the grid has at most npieces workgroups
         Piece even, odd;
-        start_piece<DIR>(a, q, even);
+        start_piece<DIR, LINES>(a, q, even);
         while (true) {
             q += step;
             if (q >= end) {
                 finish_piece<DIR, HOST_SIDE>(even);
                 return;
             }
-            start_piece<DIR>(a, q, odd);
+            start_piece<DIR, LINES>(a, q, odd);
             finish_piece<DIR, HOST_SIDE>(even);
             q += step;
             if (q >= end) {
                 finish_piece<DIR, HOST_SIDE>(odd);
                 return;
             }
-            start_piece<DIR>(a, q, even);
+            start_piece<DIR, LINES>(a, q, even);
             finish_piece<DIR, HOST_SIDE>(odd);
         }
     }
@@ -109,7 +122,10 @@ hipError_t launch_state(const StateArgs &args, Direction dir, bool host_side, hi
     if (args.npieces <= 0)
         return hipSuccess;
     const void *fn;
-    if (host_side)
+    if (host_side && args.lines)
+        fn = dir == kPack ? reinterpret_cast<const void *>(&state_kernel<kPack, true, true>)
+                          : reinterpret_cast<const void *>(&state_kernel<kUnpack, true, true>);
+    else if (host_side)
         fn = dir == kPack ? reinterpret_cast<const void *>(&state_kernel<kPack, true>)
                           : reinterpret_cast<const void *>(&state_kernel<kUnpack, true>);
     else

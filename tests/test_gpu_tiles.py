@@ -128,7 +128,7 @@ def test_planes_beyond_the_limits_of_a_launch(name, order, where, monkeypatch):
 
 
 @pytest.mark.parametrize("where", ["zero_copy", "device", "staged"])
-@pytest.mark.parametrize("page", [16, 1008, 1024, 1040, 4080, 4096, 4112, 12304])
+@pytest.mark.parametrize("page", [16, 1008, 1024, 1040, 4080, 4096, 4112, 8176, 12304, 65424, 65520])
 def test_snapshot_piece_edges(page, where):
     """Pages of one vector, next to a wave's 1 KiB and a piece's 4 KiB, and of several pieces; padded
     pages, more snapshots than one launch carries.  (Staged: a staging slot of 2 KiB, under a piece.)"""
