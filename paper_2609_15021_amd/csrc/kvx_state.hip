@@ -25,10 +25,12 @@ typedef uint32_t svec16 __attribute__((ext_vector_type(4)));
 static_assert(kStatePiece == kThreads * 16, "a piece is one vector per lane");
 
 // Workgroups of a host-side (zero-copy) launch, striding over its pieces with the next piece's reads in
-// flight, as the gather kernels' launches do.  48 pages of 3.06 MiB load at 57.0 GB/s with 16, 57.2 with 20,
-// 57.4 with 24 or 32; 16 x 36 pages of 8 KiB in 95, 94, 92 and 92 us.
+// flight, as the gather kernels' launches do.  Stores, us with 16 / 32 / 64 / 128: 4 x 8 pages of 12,896 bytes 13.3 /
+// 13.4 / 14.1 / 14.1, 4 x 8 of 16 KiB 14.6 / 14.7 / 15.5 / 15.6 (the earlier kernel 13.6 and 15.0), 48 pages of
+// 3.06 MiB 2,829 / 2,701 / 2,699 / 2,700.  Loads: 48 pages of 3.06 MiB move at 57.0 GB/s with 16, 57.2 with 20, 57.4
+// with 24 or 32; 16 x 36 pages of 8 KiB in 95, 94, 92 and 92 us.
 #ifndef KVX_STATE_HOST_WGS_PACK
-#define KVX_STATE_HOST_WGS_PACK 64
+#define KVX_STATE_HOST_WGS_PACK 32
 #endif
 #ifndef KVX_STATE_HOST_WGS_UNPACK
 #define KVX_STATE_HOST_WGS_UNPACK 24
