@@ -263,6 +263,9 @@ KV_API int32_t kv_pool_async_error(kv_pool *pool, int clear);
  * each launch's start/end events were recorded on the caller stream around it.
  * *launches, *total_ms and *bytes (algorithmic bytes: payload read + written)
  * receive the totals since the last reset (reset != 0 clears them).
+ * Launches into device staging or a device pool are bound by HBM; those of the zero-copy kernels, which
+ * zero-copy mode and the requests that KV_MODE_STAGED moves by them run, by the host link.  All count
+ * alike, so a rate taken from totals of both is neither's: KV_MODE_STAGED_DMA times staging launches only.
  */
 KV_API kv_status kv_pool_kernel_stats(kv_pool *pool, int which, int reset, int64_t *launches, double *total_ms,
                                double *bytes);

@@ -67,9 +67,10 @@ __host__ __device__ __forceinline__ int divide_long(int64_t n, int d) {
     return static_cast<int>(static_cast<double>(n) / d);
 }
 
-// Kernel arguments of one gather (pack) or scatter (unpack) launch.  A launch covers
-// chunks [chunk0, chunk0 + nchunks) of the prefix and layers [layer0, layer0 + nlayers).
-// Passed by value so that every pointer and id is captured at enqueue time.
+// Kernel arguments of one gather (pack) or scatter (unpack) launch.  A launch covers nchunks
+// consecutive chunks of the prefix and nlayers consecutive layers, from those that the block
+// table's address and plane0 name on.  Passed by value so that every pointer and id is captured
+// at enqueue time.
 struct GatherArgs {
     // What every workgroup reads, in one run (scalar loads of up to 64 bytes).
     uint8_t *chunk_base;               // device-visible address of slot 0 (pool or staging)
