@@ -433,13 +433,8 @@ def _in_use_on(t: torch.Tensor, stream) -> None:
     another stream) before that.  The allocator records an event on that stream when it frees the
     table, so a caller's own stream (a raw handle or an ExternalStream), which the caller may
     destroy first, is left out: there the caller keeps the table alive, as the C ABI requires."""
-    if stream is None:
-        s = torch.cuda.current_stream()
-    elif isinstance(stream, torch.cuda.Stream) and not isinstance(stream, torch.cuda.ExternalStream):
-        s = stream
-    else:
-        return
-    t.record_stream(s)
+    if isinstance(stream, torch.cuda.Stream) and not isinstance(stream, torch.cuda.ExternalStream):
+        t.record_stream(stream)
 
 
 def kv_check(cache: Cache, pool_layout: KvLayout, pool_slots: int, n_tokens: int, chunk_ids, for_store: bool) -> int:

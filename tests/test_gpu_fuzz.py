@@ -7,7 +7,7 @@ token-major or head-major blocks, a prefix length with partial chunks and blocks
 ids, a spare slot or two, and a staging ring of 2-3 slots of 1-3 chunks.  Cache bytes are raw
 random bytes, one device allocation per layer.  Pool and destination cache must equal the
 oracle's bytes, sentinels included.  Non-power-of-two head counts and row widths exercise the
-kernels' carry-based index walk; small rings and strided zero-copy grids exercise the engine.
+kernels' index divisions; small rings and strided zero-copy grids exercise the engine.
 
 Pools are created and destroyed per case, with tensors allocated in between: this sequence found
 that freeing physically contiguous staging corrupted later allocations (now plain device memory).
