@@ -2,7 +2,7 @@
 // of pack/unpack kernels and DMA copies against the caller's stream.
 //
 // Ordering (the dependency whose omission the paper diagnoses, Sec. 3.2 and Fig. 2):
-//  * zero-copy mode, and staged requests that move directly (kvx::moves_directly): every kernel runs on
+//  * zero-copy mode, and the staged requests that move directly (kvx::moves_directly): every kernel runs on
 //    the caller's stream, so it follows all earlier work on that stream and all later work follows it;
 //  * staged mode, store: pack kernels run on the caller's stream into staging slot k; the
 //    D2H copy of slot k runs on a side stream gated by an event recorded right after the
@@ -32,8 +32,8 @@ constexpr int kDefaultStagingSlots = 3;
 constexpr int kDefaultChunksPerBatch = 16;
 // A device pool's launches take 16 chunks, more of small ones up to 1 GiB: a launch's start and end cost
 // about 4 us.  Loads of 128k tokens in 8 MiB chunks took 1,576 us in launches of 16, 1,366-1,515 of 128; a
-// 64 MiB prefix in 256 KiB chunks 61 us in launches of 16, 27 of 256 (stores 67 and 27); 49 and 64 MiB
-// chunks the same within placement from 16 to 64.
+// 64 MiB prefix in 256 KiB chunks 61 us in launches of 16, 27 of 256 (stores 67 and 27); 49 MiB (20 to a
+// launch) and 64 MiB chunks the same within placement from 16 to 64.
 constexpr int64_t kDeviceLaunchBytes = int64_t{1} << 30;
 // One DMA side stream per direction: a store and a load in flight at once then move ~99 GB/s in total
 // (two per direction measured 57-64 GB/s: the runtime spreads their copies over more copy engines).

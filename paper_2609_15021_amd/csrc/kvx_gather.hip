@@ -44,7 +44,7 @@ typedef uint32_t vec16 __attribute__((ext_vector_type(4)));
 // Dynamic LDS (unused) reserved per workgroup of a device-side unpack, to cap the workgroups resident per
 // CU: 26 KiB of the CU's 160 KiB allows 6 (24 waves).  Paired over twelve layouts, 6 unpacked
 // 1.4% more than 8 (the hardware's limit: 32 waves) and 0.4% more than 7, and 3-4% more on the 32 KiB slabs;
-// pack lost 7% with 6 and takes no cap.
+// the fp32 layout of 64 KiB slabs loses 4% to it (6.61 -> 6.37 TB/s).  Pack lost 7% with 6 and takes no cap.
 #ifndef KVX_LDS_RESERVE_UNPACK
 #define KVX_LDS_RESERVE_UNPACK 26624
 #endif
@@ -59,8 +59,9 @@ typedef uint32_t vec16 __attribute__((ext_vector_type(4)));
 //   store by DMA copies   98.5 / 85.6 / 75.2 / 66.8 / 60.0 / 59.4   (the same at 4 KiB slabs)
 //   store by kernels      69.4 / 71.5 / 72.9 / 75.5 / 78.7 / 86.6   (within 5% at 8 and 4 KiB slabs and token-major)
 // so loads take 16 in a pool whose stores run on the DMA engines and 32 where they are kernels.  Where each lane
-// has its own block (see start_tile) the wait for its table entry also waits for a tile's data, so it
-// takes 32 for the same rate (160-byte rows: 16 move 47 GB/s, 32 move 56).
+// has its own block (see start_tile) the wait for its table entry also waits for a tile's data, and 18 are best
+// beside DMA stores (16 / 17 / 18 / 19 / 20 / 32 in total, 160-byte rows: 90.2 / 82.4 / 93.2 / 81.6 / 73.5 / 59.3;
+// 64-byte rows: 90.1 / 91.2 / 96.5 / 82.0 / 73.3 / 60.1; alone 57.0 with 18, 57.4 with 32).
 #ifndef KVX_HOST_WGS_PACK
 #define KVX_HOST_WGS_PACK 64
 #endif
@@ -69,6 +70,9 @@ typedef uint32_t vec16 __attribute__((ext_vector_type(4)));
 #endif
 #ifndef KVX_HOST_WGS_UNPACK_BESIDE_DMA
 #define KVX_HOST_WGS_UNPACK_BESIDE_DMA 16
+#endif
+#ifndef KVX_HOST_WGS_UNPACK_LANES_BESIDE_DMA
+#define KVX_HOST_WGS_UNPACK_LANES_BESIDE_DMA 18
 #endif
 #ifndef KVX_TILE_VECS
 #define KVX_TILE_VECS 256
@@ -292,10 +296,11 @@ static hipError_t launch(GatherArgs &a, Direction dir, Packed packed, hipStream_
     if (strided) {
         const int64_t total = 2 * static_cast<int64_t>(a.nlayers) *
                               ((a.nchunks - 1) * static_cast<int64_t>(a.tiles) + a.last_tiles);
-        const int64_t wgs = !host_side                           ? kStridedDeviceWgs
-                            : dir == kPack                       ? KVX_HOST_WGS_PACK
-                            : wave && packed == kInHostBesideDma ? KVX_HOST_WGS_UNPACK_BESIDE_DMA
-                                                                 : KVX_HOST_WGS_UNPACK;
+        const int64_t wgs = !host_side          ? kStridedDeviceWgs
+                            : dir == kPack      ? KVX_HOST_WGS_PACK
+                            : packed == kInHost ? KVX_HOST_WGS_UNPACK
+                            : wave              ? KVX_HOST_WGS_UNPACK_BESIDE_DMA
+                                                : KVX_HOST_WGS_UNPACK_LANES_BESIDE_DMA;
         grid = dim3(static_cast<uint32_t>(std::min(total, wgs)));
     }
     const void *fn = strided ? kernel_of<true>(dir, wave) : kernel_of<false>(dir, wave);
