@@ -248,9 +248,9 @@ inline Packed packed_in_pool(const kv_pool *pool) {
 
 // Whether a staged request of `bytes` in `copies` DMA copies moves directly instead: by the zero-copy
 // kernels on the caller's stream.  Two kinds of request are better off so.
-//  * Short ones: the staged pipeline's kernel, event, cross-queue wait and copy cost 50 to 75 us beyond the
-//    link's time, a zero-copy kernel about 20 (16 KiB stored in 85 us staged, 24 direct; 1 MiB in 92 and 41;
-//    16 MiB in 444 and 320; 32 MiB in 675 and 605).  At 32 MiB (0.6 ms) the gain is down to a tenth.
+//  * Short ones: the staged pipeline's kernel, event, cross-queue wait and copy cost 60 to 75 us beyond the
+//    link's time, a zero-copy kernel about 20 (loads in one DMA copy, us, staged and direct: 1 MiB 81 and 34,
+//    4 MiB 135 and 88, 16 MiB 359 and 309, 32 MiB 657 and 605).  At 32 MiB the gain is down to 8%.
 //  * Fragmented ones: a copy costs the DMA engine about 10 us however short (256 KiB: 18 GB/s, 1 MiB: 37,
 //    4 MiB: 50 of 57), a fifth of the time at 2 MiB a copy.  256 MiB loaded in copies of 256 KiB, 1 MiB and
 //    1.5 MiB: 17.4, 7.6 and 6.7 ms staged, 4.7 direct.
